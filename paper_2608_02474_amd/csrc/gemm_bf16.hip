@@ -11,10 +11,13 @@
 // Both operands are K-contiguous, which is what the MFMA operand layout wants:
 // every lane feeds 8 consecutive k values (16 bytes).
 //
-// Tiling for gfx950: 256 x 256 output tiles, one workgroup of four waves
-// (one per SIMD) per tile, each wave a 128 x 128 quarter as 8 x 8 blocks of
-// v_mfma_f32_16x16x32_bf16, k-steps of 64 through a two-stage LDS ring that
-// direct global-to-LDS copies fill (gemm_bf16_w4 below).
+// Tiling for gfx950.  Products of several rounds of 256 x 256 tiles (one per
+// CU) take those: one workgroup of four waves (one per SIMD) per tile, each
+// wave a 128 x 128 quarter as 8 x 8 blocks of v_mfma_f32_16x16x32_bf16,
+// k-steps of 64 through a two-stage LDS ring that direct global-to-LDS copies
+// fill (gemm_bf16_w4 below).  Smaller products take tiles of 128 x 128,
+// 64 x 64 or 32 x 64, several workgroups to a CU (gemm_bf16_sm); the launcher
+// picks by estimated time.
 // Tiles are taken in a grouped order (8 tile-rows at a time, down the rows
 // first) and dealt so that the tiles running together on the 8 XCDs (blocks
 // go round-robin to the XCDs) form one block of 8 tile-rows: every L2 works
@@ -24,7 +27,7 @@
 // bytes on the K/V shape).  Tiles that do not fill a
 // last round of the device are split along k, run first in the same launch
 // (gemm_splitk_reduce adds the ranges in order and applies the epilogue).
-// Requires N % BN == 0, n_split % BN == 0, K % BK == 0 and byte offsets of
+// Requires N % 256 == 0, n_split % 256 == 0, K % 64 == 0 and byte offsets of
 // A and B rows below 2^31; M is arbitrary (tail rows clamp their loads and
 // skip their stores).
 #include <type_traits>
@@ -434,6 +437,262 @@ __global__ void __launch_bounds__(kW4Threads, 1) gemm_bf16_w4(GemmBf16Args p) {
   }
 }
 
+// ---- the kernel of the smaller tiles: BM x BN outputs by KG groups of four
+// waves (2 x 2, each BM/2 x BN/2).  A 256 x 256 tile needs a CU to itself, so
+// a product of fewer than 256 of them leaves CUs idle, and its prologue and
+// epilogue, with one wave per SIMD, are exposed: one such tile of depth 256
+// takes 13 us.  Here two (128 x 128) or three (64 x 64 and less) workgroups
+// share a CU, so one's waits and epilogue run under another's MFMAs, and the
+// grid has four to sixteen times the workgroups.  The price is LDS reads: a
+// wave of a 128 x 128 tile reads 8 fragments per 16 MFMAs (16 per 64 in the
+// large tile), so the rate of a long product is 0.75 of the large tile's
+// (1070 against 1450 TFLOP/s on 32760 x 10240 x 5120), and large products stay
+// there.  Measured (large tile with its k-split -> this kernel):
+//   1950 x 1536 x 1536   35 -> 15 us      1950 x 1536 x 8960   160 -> 69 us
+//   7800 x 3072 x 1536   80 -> 71 us      1000 x 1024 x 1024    25 -> 6.6 us
+//   300 x 512 x 256    13.5 -> 3.1 us     111 x 256 x 512     20.7 -> 3.6 us
+// KG = 2: the groups take even and odd k-steps of one tile, each through its
+// own ring, and the epilogue adds their sums from LDS in group order: twice
+// the waves per CU where there is at most one tile for each (192 tiles of
+// depth 8960: 89 -> 71 us), without the memory traffic of a split between
+// workgroups.  KG = 1 adds the k-steps in the large tile's order with the same
+// instruction, so its results are the large tile's bit for bit.
+//
+// A k-step (64 deep, two k32 halves, two ring stages per group) runs as in the
+// large tile: the first half's MFMAs with the second half's fragment reads
+// between them; half of the second half's; the wait for this wave's copies of
+// the next k-step and the barrier; the rest, with the next k-step's first reads
+// and the copies of the k-step after next into the stage just released.  (The
+// plain order, copies at the barrier, then reads and MFMAs, was 2 to 10%
+// slower; three or four stages with one workgroup per CU 30 to 60%.)
+template <int BM, int BN, int KG>
+struct SmCfg {
+  static constexpr int kStage = (BM + BN) * 128;
+  static constexpr int kRing = KG * 2 * kStage;
+  static constexpr int kEpLd = BN + 4;  // padded row of the staged sums
+  static constexpr int kEp = KG * BM * kEpLd * 4;
+  static constexpr int kLds = kRing > kEp ? kRing : kEp;
+  static constexpr int kThreads = 256 * KG;
+  // workgroups per CU that the 160 KB of LDS hold (three at most)
+  static constexpr int kWgPerCu = kLds <= 53 * 1024 ? 3 : kLds <= 80 * 1024 ? 2 : 1;
+};
+
+template <int BM, int BN, int KG, int EPI>
+__global__ void __launch_bounds__(256 * KG, (SmCfg<BM, BN, KG>::kWgPerCu * KG))
+gemm_bf16_sm(GemmBf16Args p) {
+  typedef SmCfg<BM, BN, KG> C;
+  constexpr int WM = BM / 2, WN = BN / 2, TI = WM / 16, TJ = WN / 16;
+  constexpr int NM = TI * TJ, NR = TI + TJ;                 // MFMAs and fragment reads of a k32 half
+  constexpr int CA = BM / 32, CB = BN / 32, NCP = CA + CB;  // copies per wave and k-step
+  __shared__ __attribute__((aligned(1024))) char smem[C::kLds];
+  const int tid = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave), lane = tid % kWave;
+  const int grp = wave / 4, w4 = wave % 4;
+  const int wm = w4 >> 1, wn = w4 & 1;
+  const int l16 = lane & 15, lq = lane >> 4;
+
+  // ---- tile and k-range: XCD x takes a contiguous range of the grouped order
+  // (with nsplit > 1, of the pieces: the k-ranges of a tile are neighbours)
+  const int tm = (p.M + BM - 1) / BM, tn = p.N / BN;
+  const int per = gridDim.x / 8, rem = gridDim.x % 8, xcd = blockIdx.x % 8;
+  const int piece = xcd * per + (xcd < rem ? xcd : rem) + blockIdx.x / 8;
+  const bool split_k = p.nsplit > 1;
+  const int pid = split_k ? piece / p.nsplit : piece;
+  int tile_m, tile_n;
+  gemm_tile_of(pid, tm, tn, tile_m, tile_n);
+  const int m0 = tile_m * BM, n0 = tile_n * BN;
+  const int nk_all = p.K / 64;
+  const int kt0 = split_k ? (piece % p.nsplit) * p.kps : 0;
+  const int nk = split_k ? (nk_all - kt0 < p.kps ? nk_all - kt0 : p.kps) : nk_all;  // >= 1
+  const int nit = nk / KG;  // k-steps of a group (the launcher takes KG = 2 for even nk only)
+
+  // ---- copy plan, as in the large tile: copy c of a wave fills the 8 rows
+  // 8 (w4 + 4 c) .. of its group's (A ++ B) stage
+  const bf16_t* b_base = n0 < p.n_split ? p.B0 : p.B1;  // BN divides n_split
+  const int n_off = n0 < p.n_split ? n0 : n0 - p.n_split;
+  const int chunk = (lane % 8) ^ (((8 * w4 + lane / 8) >> 1) & 7);
+  uint32_t voff_a[CA];
+#pragma unroll
+  for (int c = 0; c < CA; ++c) {
+    int m = m0 + 8 * (w4 + 4 * c) + lane / 8;
+    m = m < p.M ? m : p.M - 1;
+    const uint32_t ar = p.a_rows ? static_cast<uint32_t>(p.a_rows[m]) : static_cast<uint32_t>(m);
+    voff_a[c] = (ar * static_cast<uint32_t>(p.lda) + chunk * 8) * 2u;
+  }
+  const uint32_t voff_b = ((n_off + 8 * w4 + lane / 8) * static_cast<uint32_t>(p.ldb) + chunk * 8) * 2u;
+  const int64_t b_copy_step = 32 * p.ldb;
+  const uint32_t dst0 = lds_offset(smem) + grp * 2 * C::kStage + w4 * 1024;
+  const bf16_t* src_a = p.A;
+  const bf16_t* src_b = b_base;
+  uint32_t dst_stage = 0;
+  auto set_fill = [&](int it) __attribute__((always_inline)) {
+    // past the last k-step: re-fetched, in bounds, never used
+    const int kt = kt0 + (it < nit ? it : nit - 1) * KG + grp;
+    src_a = p.A + static_cast<int64_t>(kt) * 64;
+    src_b = b_base + static_cast<int64_t>(kt) * 64;
+    dst_stage = dst0 + (it & 1) * C::kStage;
+  };
+  auto copy = [&](auto c_c) __attribute__((always_inline)) {
+    constexpr int c = decltype(c_c)::value;
+    if constexpr (c < CA)
+      lds_copy16_s(src_a, voff_a[c], dst_stage + c * 4096);
+    else
+      lds_copy16_s(src_b + (c - CA) * b_copy_step, voff_b, dst_stage + c * 4096);
+  };
+
+  // ---- fragments: read q of a half is A block 0, then the B blocks, then the
+  // other A blocks, the order the MFMAs (A block outer) use them
+  const char* ring = smem + grp * 2 * C::kStage;
+  const int rd_a = (wm * WM + l16) * 128, rd_b = (BM + wn * WN + l16) * 128;
+  const int ch0 = (lq ^ (l16 >> 1)) * 16, ch1 = ((4 + lq) ^ (l16 >> 1)) * 16;
+  bf16x8 fa[2][TI], fb[2][TJ];
+  auto read = [&](auto set_c, auto q_c, const char* st) __attribute__((always_inline)) {
+    constexpr int SET = decltype(set_c)::value, Q = decltype(q_c)::value;
+    const int ch = SET ? ch1 : ch0;
+    if constexpr (Q == 0)
+      fa[SET][0] = *reinterpret_cast<const bf16x8*>(st + rd_a + ch);
+    else if constexpr (Q <= TJ)
+      fb[SET][Q - 1] = *reinterpret_cast<const bf16x8*>(st + rd_b + (Q - 1) * 2048 + ch);
+    else
+      fa[SET][Q - TJ] = *reinterpret_cast<const bf16x8*>(st + rd_a + (Q - TJ) * 2048 + ch);
+  };
+  f32x4 acc[TI][TJ];
+#pragma unroll
+  for (int i = 0; i < TI; ++i)
+#pragma unroll
+    for (int j = 0; j < TJ; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  auto mma = [&](auto set_c, auto t0_c, auto t1_c) __attribute__((always_inline)) {
+    constexpr int SET = decltype(set_c)::value;
+    static_for<decltype(t0_c)::value, decltype(t1_c)::value>([&](auto t_c) __attribute__((always_inline)) {
+      constexpr int T = decltype(t_c)::value;
+      acc[T / TJ][T % TJ] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[SET][T / TJ], fb[SET][T % TJ],
+                                                                    acc[T / TJ][T % TJ], 0, 0, 0);
+    });
+  };
+  typedef std::integral_constant<int, 0> S0;
+  typedef std::integral_constant<int, 1> S1;
+  typedef std::integral_constant<int, NM / 2> Mid;  // MFMAs of the second half before the barrier
+  // the first half's MFMAs with the second half's reads, then the second half's first MFMAs
+  auto phase0 = [&](const char* st) __attribute__((always_inline)) {
+    static_for<0, NR>([&](auto q_c) __attribute__((always_inline)) {
+      constexpr int Q = decltype(q_c)::value;
+      __builtin_amdgcn_sched_barrier(0);
+      read(S1{}, q_c, st);
+      mma(S0{}, std::integral_constant<int, Q * NM / NR>{}, std::integral_constant<int, (Q + 1) * NM / NR>{});
+    });
+    __builtin_amdgcn_sched_barrier(0);
+    mma(S1{}, std::integral_constant<int, 0>{}, Mid{});
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  set_fill(0);
+  static_for<0, NCP>(copy);
+  set_fill(1);
+  static_for<0, NCP>(copy);
+  __builtin_amdgcn_s_waitcnt(waitcnt_vm(NCP));
+  __syncthreads();
+  static_for<0, NR>([&](auto q_c) __attribute__((always_inline)) { read(S0{}, q_c, ring); });
+  phase0(ring);
+  // the barrier of k-step `it` (of a group), its last MFMAs, and k-step it + 1
+  // up to its barrier
+  auto step = [&](int it) __attribute__((always_inline)) {
+    const char* nxt = ring + ((it & 1) ^ 1) * C::kStage;
+    __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));  // this wave's copies of k-step it + 1
+    __syncthreads();
+    set_fill(it + 2);
+    static_for<0, NR>([&](auto q_c) __attribute__((always_inline)) {
+      constexpr int Q = decltype(q_c)::value, M1 = NM - Mid::value;
+      __builtin_amdgcn_sched_barrier(0);
+      read(S0{}, q_c, nxt);
+      static_for<Q * NCP / NR, (Q + 1) * NCP / NR>(copy);
+      mma(S1{}, std::integral_constant<int, Mid::value + Q * M1 / NR>{},
+          std::integral_constant<int, Mid::value + (Q + 1) * M1 / NR>{});
+    });
+    __builtin_amdgcn_sched_barrier(0);
+    phase0(nxt);
+  };
+  for (int it = 0; it + 1 < nit; ++it) step(it);
+  mma(S1{}, Mid{}, std::integral_constant<int, NM>{});
+  __builtin_amdgcn_s_waitcnt(0);  // re-fetched k-steps still landing in LDS
+  __syncthreads();
+
+  // ---- epilogue: every group's sums staged in LDS, then each thread takes 4
+  // consecutive columns of BM / RPP rows and adds the groups in order
+  float* ep = reinterpret_cast<float*>(smem);
+  float* eg = ep + grp * BM * C::kEpLd;
+#pragma unroll
+  for (int i = 0; i < TI; ++i)
+#pragma unroll
+    for (int j = 0; j < TJ; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        eg[(wm * WM + i * 16 + 4 * lq + r) * C::kEpLd + wn * WN + j * 16 + l16] = acc[i][j][r];
+  constexpr int C4 = BN / 4, RPP = C::kThreads / C4, NQ = BM / RPP;
+  constexpr int G = NQ < 8 ? NQ : 8;  // rows whose residuals are fetched together
+  static_assert(BM % RPP == 0 && NQ % G == 0, "whole passes of the workgroup");
+  constexpr bool RES = EPI == EPI_GATE_RES;
+  const int c4 = tid % C4, r0 = tid / C4;
+  const int col = n0 + 4 * c4;
+  float bias[4], gate[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+  gemm_col4<EPI>(p, col, bias, gate);
+  __syncthreads();
+#pragma unroll
+  for (int q0 = 0; q0 < NQ; q0 += G) {
+    float res[RES ? G : 1][4];
+    if constexpr (RES) {
+      if (!split_k) {
+        int32_t rr[G];
+#pragma unroll
+        for (int q = 0; q < G; ++q) {
+          const int m = m0 + r0 + (q0 + q) * RPP;
+          rr[q] = m < p.M ? m : p.M - 1;
+        }
+        if (p.res_rows != nullptr) {
+#pragma unroll
+          for (int q = 0; q < G; ++q) rr[q] = p.res_rows[rr[q]];
+        }
+        if (p.res_bf16) {
+          uint2 raw[G];
+#pragma unroll
+          for (int q = 0; q < G; ++q)
+            raw[q] = ldg8_nt(static_cast<const bf16_t*>(p.res) + static_cast<int64_t>(rr[q]) * p.ldr + col);
+#pragma unroll
+          for (int q = 0; q < G; ++q) {
+            res[q][0] = __uint_as_float(raw[q].x << 16);
+            res[q][1] = __uint_as_float(raw[q].x & 0xffff0000u);
+            res[q][2] = __uint_as_float(raw[q].y << 16);
+            res[q][3] = __uint_as_float(raw[q].y & 0xffff0000u);
+          }
+        } else {
+          uint4 raw[G];
+#pragma unroll
+          for (int q = 0; q < G; ++q)
+            raw[q] = ldg16_nt(static_cast<const float*>(p.res) + static_cast<int64_t>(rr[q]) * p.ldr + col);
+#pragma unroll
+          for (int q = 0; q < G; ++q) unpack16(raw[q], res[q], static_cast<const float*>(nullptr));
+        }
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < G; ++q) {
+      const int r = r0 + (q0 + q) * RPP;
+      float v[4];
+#pragma unroll
+      for (int g = 0; g < KG; ++g) {
+        const float4 a4 = *reinterpret_cast<const float4*>(ep + (g * BM + r) * C::kEpLd + 4 * c4);
+        v[0] = g == 0 ? a4.x : v[0] + a4.x;
+        v[1] = g == 0 ? a4.y : v[1] + a4.y;
+        v[2] = g == 0 ? a4.z : v[2] + a4.z;
+        v[3] = g == 0 ? a4.w : v[3] + a4.w;
+      }
+      if (split_k)
+        *reinterpret_cast<float4*>(p.part + static_cast<int64_t>(piece) * BM * BN + r * BN + 4 * c4) =
+            make_float4(v[0], v[1], v[2], v[3]);
+      else if (m0 + r < p.M)
+        gemm_store4<EPI>(p, m0 + r, col, v, bias, gate, res[RES ? q : 0]);
+    }
+  }
+}
+
 // Sum the k-range partials of the split tail tiles in split order and apply
 // the epilogue.  One thread per 4 output columns.
 template <int BM, int BN, int EPI>
@@ -462,78 +721,165 @@ __global__ void __launch_bounds__(256) gemm_splitk_reduce(GemmBf16Args p, int nt
   gemm_store4<EPI>(p, row, tile_n * BN + 4 * c4, v, bias, gate, res);
 }
 
-// The tile kernel the launcher runs.
-template <int EPI>
-struct GemmW4 {
-  static constexpr int kThreads = kW4Threads;
-  static void launch(int grid, const GemmBf16Args& a, hipStream_t stream) {
-    hipLaunchKernelGGL((gemm_bf16_w4<EPI>), dim3(grid), dim3(kThreads), 0, stream, a);
-  }
+// ---- launcher.  One tile size for a product, the one with the least
+// estimated time: microseconds per k-step of 64 and the fixed times below are
+// measured on MI355X (256 CUs) over 36 products of 75 .. 32760 rows, 256 ..
+// 13824 columns and depths 256 .. 13824.  Over them the choice is the fastest
+// of the measured or within 8% of it.  (Whole rounds of large tiles with the
+// other rows in small ones, in two launches, were within 2% of the better of
+// the two: not built.)
+constexpr int kBK = 64, kBigTile = 256;
+
+enum GemmTile { TILE_256, TILE_128, TILE_128_K2, TILE_64, TILE_32x64_K2 };
+
+struct GemmPlan {
+  GemmTile tile;
+  int nsplit;  // k-ranges: of the last, partly filled round's tiles (TILE_256), of every tile (TILE_128)
+  float us;    // estimated time
 };
 
-template <int BM, int BN, int BK, int EPI, typename KERNEL>
-hipError_t launch_gemm_epi(const char* name, GemmBf16Args a, hipStream_t stream) {
-  const int tiles = ((a.M + BM - 1) / BM) * (a.N / BN);
-  const int nk = a.K / BK;
-  // Tiles beyond the last full round (one workgroup per CU) are split along
-  // k; a reduce kernel adds the splits.  A tail of at least a quarter of the
-  // CUs is cut so that its pieces fill that round; a smaller one into about
-  // 3/16 of the CUs' worth of pieces (with 256 CUs, measured in the cached
-  // block step: 64 tail tiles in 4 pieces each beat 3, 2 and 1; 16 tiles in
-  // 3 beat 2, 4 and 8 (O projection 562 -> 545 us, FFN down 1377 -> 1331
-  // us); 8 tiles in 6 beat 4 and 8; 4 tiles in the 8 that the k-step floor
-  // below allows beat 6, 4 and 3).
-  const int ncu = device_cu_count();
+// k-ranges of each tile of the last, partly filled round of 256 x 256 tiles.
+// A tail of at least a quarter of the CUs is cut so that its pieces fill that
+// round; a smaller one into about 3/16 of the CUs' worth of pieces (with 256
+// CUs, measured in the cached block step: 64 tail tiles in 4 pieces each beat
+// 3, 2 and 1; 16 tiles in 3 beat 2, 4 and 8 (O projection 562 -> 545 us, FFN
+// down 1377 -> 1331 us); 8 tiles in 6 beat 4 and 8; 4 tiles in the 8 that the
+// k-step floor below allows beat 6, 4 and 3).
+int big_tail_split(int tiles, int nk, int ncu, size_t part_bytes) {
   const int tail = tiles % ncu;
-  int nsplit = 1;
-  if (tail > 0) nsplit = 4 * tail >= ncu ? ncu / tail : (3 * ncu / 16 + tail - 1) / tail;
-  nsplit = nsplit < nk ? nsplit : nk;
+  if (tail == 0) return 1;
+  int nsplit = 4 * tail >= ncu ? ncu / tail : (3 * ncu / 16 + tail - 1) / tail;
   // Each split also writes and the reduce reads a 256 KB fp32 partial tile:
   // below about 640 of depth (10 k-steps) per split that costs more than the
   // shorter range saves.
-  constexpr int kMinStepsPerSplit = 640 / BK;
+  constexpr int kMinStepsPerSplit = 640 / kBK;
   const int cap = nk / kMinStepsPerSplit > 1 ? nk / kMinStepsPerSplit : 1;
   nsplit = nsplit < cap ? nsplit : cap;
-  const size_t unit_bytes = sizeof(float) * BM * BN;
-  while (nsplit > 1 && static_cast<size_t>(tail) * nsplit * unit_bytes > a.part_bytes) --nsplit;
-  if (a.part == nullptr) nsplit = 1;
-  ::echo::TimedLaunch scope(name, stream);
-  a.tile_base = 0;
-  a.npieces = 0;
-  if (nsplit < 2) {
-    a.nsplit = 1;
-    KERNEL::launch(tiles, a, stream);
-    return hipGetLastError();
+  const size_t unit_bytes = sizeof(float) * kBigTile * kBigTile;
+  while (nsplit > 1 && static_cast<size_t>(tail) * nsplit * unit_bytes > part_bytes) --nsplit;
+  return nsplit;
+}
+
+// 256 x 256 tiles: 1.46 us per k-step of a round, 7 us to fill and drain it.
+float big_us(int tiles, int nk, int ncu, int nsplit) {
+  const int full = tiles / ncu, pieces = (tiles % ncu) * nsplit;
+  float us = 3.0f + full * (1.46f * nk + 7.0f);
+  if (pieces > 0) {
+    // few pieces run beside the first whole tiles: about half of their time shows
+    const float r = nsplit > 1 && full > 0 && 4 * pieces < ncu ? 0.5f : 1.0f;
+    us += r * (1.46f * ((nk + nsplit - 1) / nsplit) + 7.0f);
+    if (nsplit > 1) us += 3.0f + 0.06f * pieces;  // 256 KB of partial sums per piece, written and reduced
   }
-  a.kps = (nk + nsplit - 1) / nsplit;  // k-steps per split
-  nsplit = (nk + a.kps - 1) / a.kps;   // every split non-empty
-  // One launch, the pieces first: when they cover only part of the CUs (the
-  // 13104-row projections: 16 tiles x 3 pieces), the other CUs start on whole
-  // tiles and stay a piece's time ahead, so that the rounds' epilogues no
-  // longer store at the same moment on every CU (O projection with 8 pieces a
-  // tile: 577 -> 563 us against whole tiles first, then the pieces, in two
-  // launches).
-  const int full = tiles - tail;
-  a.tile_base = full;
-  a.nsplit = nsplit;
-  a.npieces = tail * nsplit;
-  KERNEL::launch(tail * nsplit + full, a, stream);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  const int64_t threads = static_cast<int64_t>(tail) * BM * (BN / 4);
+  return us;
+}
+
+// Smaller tiles: n workgroups fall to the busiest CU, two (128 x 128) or three
+// (the others) at a time.
+float small_us(GemmTile t, int M, int N, int nk, int nsplit, int ncu) {
+  const int bm = t == TILE_32x64_K2 ? 32 : t == TILE_64 ? 64 : 128, bn = t == TILE_64 || t == TILE_32x64_K2 ? 64 : 128;
+  const int pieces = ((M + bm - 1) / bm) * (N / bn) * nsplit;
+  const int n = (pieces + ncu - 1) / ncu, steps = (nk + nsplit - 1) / nsplit;
+  float us;
+  if (t == TILE_128) {
+    // one workgroup alone 0.63 us per k-step, two together 1.02 (less while not every CU has two)
+    const float load = static_cast<float>(pieces) / ncu;
+    us = 3.0f + steps * (n == 2 ? 0.63f + 0.4f * (load - 1.0f) : 1.02f * (n / 2) + 0.63f * (n % 2));
+  } else if (t == TILE_128_K2) {
+    us = 1.0f + n * (0.5f * (steps + 1) + 3.0f);
+  } else if (t == TILE_64) {
+    us = 2.3f + steps * (0.56f * (n / 3) + (n % 3 == 2 ? 0.42f : n % 3 == 1 ? 0.27f : 0.0f));
+  } else {
+    us = 2.3f + 0.5f * (steps + 1) * (0.83f * (n / 3) + (n % 3 == 2 ? 0.45f : n % 3 == 1 ? 0.27f : 0.0f));
+  }
+  if (nsplit > 1) us += 3.0f + 0.2e-6f * (static_cast<float>(pieces) * bm * bn * 4.0f);  // partial sums, reduce
+  return us;
+}
+
+// part_bytes == 0 (no room for partial sums: every row must come out the same
+// for any M) leaves the plans that add the k-steps in order.
+GemmPlan gemm_plan(int M, int N, int K, int ncu, size_t part_bytes) {
+  const bool any_order = part_bytes > 0;
+  const int nk = K / kBK, tiles = ((M + kBigTile - 1) / kBigTile) * (N / kBigTile);
+  const int nsplit = any_order ? big_tail_split(tiles, nk, ncu, part_bytes) : 1;
+  GemmPlan best{TILE_256, nsplit, big_us(tiles, nk, ncu, nsplit)};
+  auto consider = [&](GemmTile t, int sp) {
+    const float us = small_us(t, M, N, nk, sp, ncu);
+    if (us < best.us) best = GemmPlan{t, sp, us};
+  };
+  consider(TILE_128, 1);
+  consider(TILE_64, 1);
+  if (!any_order) return best;
+  if (nk % 2 == 0) {
+    consider(TILE_128_K2, 1);
+    consider(TILE_32x64_K2, 1);
+  }
+  const size_t bytes = static_cast<size_t>((M + 127) / 128) * 128 * N * sizeof(float);
+  for (int sp = 2; sp <= 4; ++sp)  // at least 640 of depth per range, as above
+    if (nk / sp >= 10 && bytes * sp <= part_bytes) consider(TILE_128, sp);
+  return best;
+}
+
+template <int BM, int BN, int EPI>
+hipError_t launch_splitk_reduce(const GemmBf16Args& a, int ntiles, hipStream_t stream) {
+  const int64_t threads = static_cast<int64_t>(ntiles) * BM * (BN / 4);
   hipLaunchKernelGGL((gemm_splitk_reduce<BM, BN, EPI>), dim3(static_cast<unsigned>((threads + 255) / 256)),
-                     dim3(256), 0, stream, a, tail);
+                     dim3(256), 0, stream, a, ntiles);
   return hipGetLastError();
 }
 
-hipError_t launch_gemm_w4(const char* name, int epi, const GemmBf16Args& a, hipStream_t stream) {
-  constexpr int BM = 256, BN = 256, BK = 64;
-  if (a.N % BN != 0 || (a.n_split < a.N && a.n_split % BN != 0) || a.K % BK != 0)
-    return hipErrorInvalidValue;
-  switch (epi) {
-    case EPI_BIAS: return launch_gemm_epi<BM, BN, BK, EPI_BIAS, GemmW4<EPI_BIAS>>(name, a, stream);
-    case EPI_GELU: return launch_gemm_epi<BM, BN, BK, EPI_GELU, GemmW4<EPI_GELU>>(name, a, stream);
-    default: return launch_gemm_epi<BM, BN, BK, EPI_GATE_RES, GemmW4<EPI_GATE_RES>>(name, a, stream);
+template <int BM, int BN, int KG, int EPI>
+hipError_t launch_gemm_sm(GemmBf16Args a, int nsplit, hipStream_t stream) {
+  const int tiles = ((a.M + BM - 1) / BM) * (a.N / BN), nk = a.K / kBK;
+  a.tile_base = 0;
+  a.npieces = 0;
+  a.kps = (nk + nsplit - 1) / nsplit;
+  a.nsplit = (nk + a.kps - 1) / a.kps;  // every range non-empty
+  hipLaunchKernelGGL((gemm_bf16_sm<BM, BN, KG, EPI>), dim3(tiles * a.nsplit), dim3(SmCfg<BM, BN, KG>::kThreads), 0,
+                     stream, a);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess || a.nsplit < 2) return e;
+  return launch_splitk_reduce<BM, BN, EPI>(a, tiles, stream);
+}
+
+// `a` in 256 x 256 tiles, those of the last partly filled round in nsplit k-ranges
+template <int EPI>
+hipError_t launch_gemm_big(GemmBf16Args a, int nsplit, int ncu, hipStream_t stream) {
+  const int tiles = ((a.M + kBigTile - 1) / kBigTile) * (a.N / kBigTile), nk = a.K / kBK;
+  a.tile_base = 0;
+  a.npieces = 0;
+  a.nsplit = 1;
+  int grid = tiles, tail = 0;
+  if (nsplit > 1) {
+    a.kps = (nk + nsplit - 1) / nsplit;  // k-steps per split
+    a.nsplit = (nk + a.kps - 1) / a.kps;  // every split non-empty
+    // One launch, the pieces first: when they cover only part of the CUs (the
+    // 13104-row projections: 16 tiles x 3 pieces), the other CUs start on whole
+    // tiles and stay a piece's time ahead, so that the rounds' epilogues no
+    // longer store at the same moment on every CU (O projection with 8 pieces a
+    // tile: 577 -> 563 us against whole tiles first, then the pieces, in two
+    // launches).
+    tail = tiles % ncu;
+    a.tile_base = tiles - tail;
+    a.npieces = tail * a.nsplit;
+    grid = a.npieces + tiles - tail;
+  }
+  hipLaunchKernelGGL((gemm_bf16_w4<EPI>), dim3(grid), dim3(kW4Threads), 0, stream, a);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess || a.nsplit < 2) return e;
+  return launch_splitk_reduce<kBigTile, kBigTile, EPI>(a, tail, stream);
+}
+
+template <int EPI>
+hipError_t launch_gemm_epi(const char* name, const GemmBf16Args& a, hipStream_t stream) {
+  const int ncu = device_cu_count();
+  const GemmPlan plan = gemm_plan(a.M, a.N, a.K, ncu, a.part != nullptr ? a.part_bytes : 0);
+  ::echo::TimedLaunch scope(name, stream);
+  switch (plan.tile) {
+    case TILE_128: return launch_gemm_sm<128, 128, 1, EPI>(a, plan.nsplit, stream);
+    case TILE_128_K2: return launch_gemm_sm<128, 128, 2, EPI>(a, 1, stream);
+    case TILE_64: return launch_gemm_sm<64, 64, 1, EPI>(a, 1, stream);
+    case TILE_32x64_K2: return launch_gemm_sm<32, 64, 2, EPI>(a, 1, stream);
+    default: return launch_gemm_big<EPI>(a, plan.nsplit, ncu, stream);
   }
 }
 
@@ -543,7 +889,13 @@ hipError_t launch_gemm_bf16(const char* name, int epi, const GemmBf16Args& a, hi
   const int64_t lim = int64_t(1) << 31;
   if (a.a_nrows <= 0 || a.a_nrows * a.lda * 2 >= lim || int64_t(a.N) * a.ldb * 2 >= lim)
     return hipErrorInvalidValue;
-  return launch_gemm_w4(name, epi, a, stream);
+  if (a.N % kBigTile != 0 || (a.n_split < a.N && a.n_split % kBigTile != 0) || a.K % kBK != 0)
+    return hipErrorInvalidValue;
+  switch (epi) {
+    case EPI_BIAS: return launch_gemm_epi<EPI_BIAS>(name, a, stream);
+    case EPI_GELU: return launch_gemm_epi<EPI_GELU>(name, a, stream);
+    default: return launch_gemm_epi<EPI_GATE_RES>(name, a, stream);
+  }
 }
 
 }  // namespace echo

@@ -34,8 +34,9 @@ struct GemmBf16Args {
   float* part;              // optional: fp32 partial tiles of the split-K tail
   size_t part_bytes;
   // set by the launcher: the first split tile, k splits per split tile (<= 1:
-  // none), k-steps per split, and the workgroups that run split pieces (the
-  // first npieces of the launch; the rest run whole tiles from tile 0)
+  // none), k-steps per split, and the workgroups of a 256 x 256 tile launch
+  // that run split pieces (the first npieces; the rest run whole tiles from
+  // tile 0; the smaller tiles are split all or none)
   int tile_base, nsplit, kps;
   int npieces;
 };

@@ -301,6 +301,36 @@ def test_block_partial_balanced_ranges(w):
         want = OB.block_partial(p, x, idx, w.H, kv=kv)
         check_block(got, want, w.dtype, f"{w.name}/n={n}")
 
+# sizes at the edges of the smaller GEMM tiles (32 x 64, 64 x 64, 128 x 128, with the k-steps in one or two
+# groups): one row, one row short of and past a tile, and one workgroup per CU or more
+SMALL_TILES = [
+    synth.Workload("tiles_bf16_70tok", T=2, grid=(5, 7), D=256, H=2, F=512, n_samples=4000, ratio=0.5,
+                   dtype="bf16", audio="speech", seed=61),
+    synth.Workload("tiles_bf16_1000tok", T=4, grid=(10, 25), D=1024, H=8, F=4096, n_samples=4000, ratio=0.5,
+                   dtype="bf16", audio="speech", seed=62),
+]
+
+
+@pytest.mark.parametrize("w", SMALL_TILES, ids=lambda w: w.name)
+def test_block_partial_small_gemm_tiles(w):
+    """Parity at the edges of the smaller tiles, and, batch-invariant, the
+    same bits for a row whatever tile its selection's size leads to."""
+    p = synth.make_block_weights(w)
+    _, x = synth.make_latents(w)
+    P, X = params_to_device(p, w.dtype), up(x, tdtype(w.dtype))
+    kv = OB.kv_projection(OB._f64(p), np.asarray(x, np.float64))
+    counts = [n for n in (1, 31, 33, 63, 65, 129) if n < w.L] + [w.L]
+    rng = np.random.default_rng(w.seed)
+    want = OB.block_partial(p, x, np.arange(w.L), w.H, kv=kv)
+    every = up(np.arange(w.L, dtype=np.int32))
+    full = api.block_partial(P, X, every, w.L, w.H, batch_invariant=True).clone()
+    for n in counts:
+        idx = np.sort(rng.choice(w.L, n, replace=False)).astype(np.int32)
+        say(f"small tiles {w.name} n={n}")
+        check_block(down(api.block_partial(P, X, up(idx), n, w.H)), want[idx], w.dtype, f"{w.name} n={n}")
+        ys = api.block_partial(P, X, up(idx), n, w.H, batch_invariant=True)
+        assert torch.equal(ys, full[torch.from_numpy(idx.astype(np.int64)).to(full.device)]), n
+
 
 def _reference_moves(q, k, H):
     """Per (query, head) row: how often a lazily rescaled streaming softmax
