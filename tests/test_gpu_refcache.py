@@ -92,3 +92,27 @@ def test_refcache_tau_extremes():
 def test_refcache_full_size():
     # the 32760-token 14B-shaped block, chains of one latent-grid row (52 tokens)
     _run(L=32760, D=5120, chain_len=52, tau=0.5, dtype="bf16", steps=2, seed=6)
+
+
+@pytest.mark.parametrize("D,dtype", [(1024, "f32"), (3080, "bf16"), (5120, "f32"), (8184, "bf16"), (16384, "bf16")])
+def test_refcache_row_widths(D, dtype):
+    # every register width of the update kernel, full and one chunk short of it
+    _run(L=48, D=D, chain_len=6, tau=0.4, dtype=dtype, steps=3, seed=7)
+
+
+def test_refcache_nothing_rewritten():
+    # no chains to scan: every row rebuilt from its entry, state untouched
+    L, D = 40, 520
+    rng = np.random.default_rng(8)
+    gpu = api.RefCache(L, D, 8, 0.4, torch.bfloat16, device())
+    xref = torch.zeros((L, D), dtype=torch.bfloat16, device=device())
+    x, idx = up(rng.standard_normal((L, D)).astype(np.float32), torch.bfloat16), up(np.arange(L, dtype=np.int32))
+    ones = torch.ones(L, dtype=torch.uint8, device=device())
+    y0 = _rows_around(rng, rng.standard_normal((L // 8, D)), np.arange(L), 8, np.full(L, 0.8))
+    gpu.update(x, idx, ones, L, up(y0), xref)
+    read = gpu.update(x, idx, torch.zeros_like(ones), 0, None, xref).clone()
+    ora = RefCache(L, D, 8, 0.4, "bf16")
+    _, xr = step_update(ora, down(x), np.arange(L), y0, np.zeros((L, D), np.float32))
+    want, _ = step_update(ora, down(x), np.zeros(0, np.int64), np.zeros((0, D), np.float32), xr)
+    assert np.array_equal(down(read), want) and np.array_equal(down(xref), xr)
+    assert gpu.live_refs() == ora.live_refs()
