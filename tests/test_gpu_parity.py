@@ -332,6 +332,38 @@ def test_block_partial_small_gemm_tiles(w):
         assert torch.equal(ys, full[torch.from_numpy(idx.astype(np.int64)).to(full.device)]), n
 
 
+# fp32 shapes at the edges of the 16 x 16 and 32 x 32 tiles, of the 16-key groups and of the depth's chunks of
+# 16: head widths 10, 12, 88 and 128 (padded and whole), widths 8 past a multiple of 16, 1 to 330 tokens
+F32_EDGE = [
+    synth.Workload("f32_w10_17tok", T=1, grid=(1, 17), D=40, H=4, F=72, n_samples=4000, ratio=0.5, dtype="f32",
+                   audio="speech", seed=71),
+    synth.Workload("f32_w12_1tok", T=1, grid=(1, 1), D=24, H=2, F=24, n_samples=4000, ratio=0.5, dtype="f32",
+                   audio="speech", seed=72),
+    synth.Workload("f32_w88_65tok", T=5, grid=(1, 13), D=264, H=3, F=520, n_samples=4000, ratio=0.5, dtype="f32",
+                   audio="speech", seed=73),
+    synth.Workload("f32_w128_330tok", T=3, grid=(10, 11), D=512, H=4, F=1544, n_samples=4000, ratio=0.5, dtype="f32",
+                   audio="speech", seed=74),
+]
+
+
+@pytest.mark.parametrize("w", F32_EDGE, ids=lambda w: w.name)
+def test_block_partial_f32_edges(w):
+    """Every selected row at the fp32 bar, and the same bits for a row in any
+    selection (the tile and the workgroups do not change its sums)."""
+    p = synth.make_block_weights(w)
+    _, x = synth.make_latents(w)
+    P, X = params_to_device(p, w.dtype), up(x, tdtype(w.dtype))
+    kv = OB.kv_projection(OB._f64(p), np.asarray(x, np.float64))
+    want = OB.block_partial(p, x, np.arange(w.L), w.H, kv=kv)
+    full = api.block_partial(P, X, up(np.arange(w.L, dtype=np.int32)), w.L, w.H).clone()
+    check_block(down(full), want, w.dtype, w.name)
+    rng = np.random.default_rng(w.seed)
+    for n in sorted({n for n in (1, 15, 16, 33) if n < w.L}):
+        idx = np.sort(rng.choice(w.L, n, replace=False)).astype(np.int32)
+        ys = api.block_partial(P, X, up(idx), n, w.H)
+        assert torch.equal(ys, full[torch.from_numpy(idx.astype(np.int64)).to(full.device)]), n
+
+
 def _reference_moves(q, k, H):
     """Per (query, head) row: how often a lazily rescaled streaming softmax
     moves its reference over the keys in 32-key halves (the reference starts
