@@ -722,6 +722,174 @@ attn_fwd_bf16(const bf16_t* __restrict__ q, int64_t ldq, const bf16_t* __restric
   }  // fragments
 }
 
+// ---- few queries and few keys.  The kernel above walks all keys of its
+// queries in one workgroup, behind a ring that has to fill first: a block of
+// 300 tokens is two workgroups, one of 1560 tokens with 600 selected and 12
+// heads 24, on 256 CUs.  Here a workgroup takes 32 queries of a head and its
+// 8 waves divide the keys: wave w holds the 32-key blocks w, w + 8, ..., with
+// a streaming softmax of its own, and the partial results are merged in LDS
+// in wave order.  Waves never wait for each other in the loop: each reads its
+// K fragments straight from L2 into registers and its V block into a private
+// LDS buffer (two, direct copies), one block ahead of the one it works on.
+// The price is that K and V reach a CU once per 32 queries, and that a K
+// fragment read touches 32 rows (2.3 us per block, bound by those accesses), so
+// it pays only where the chip is otherwise idle (att_choose).  Same arithmetic
+// as above: bf16 probabilities, row sums of the rounded values, the reference
+// moved only when a block's maximum exceeds it by more than 2^8.
+//   111 queries x 300 keys x 2 heads 10.8 -> 8.6 us, 600 x 1560 x 12 57 -> 22,
+//   1000 x 1000 x 8 40 -> 16 (whole 384-query items -> this kernel)
+constexpr int ATT_S_WAVES = 8;
+constexpr int ATT_S_VBUF = 32 * ATT_DH * 2;  // a 32-key block of V: 8 KB
+
+__global__ void __launch_bounds__(ATT_S_WAVES * 64, 2)
+attn_short_bf16(const bf16_t* __restrict__ q, int64_t ldq, const bf16_t* __restrict__ k,
+                const bf16_t* __restrict__ v, int64_t ldkv, int Mq, int L, float scale_log2,
+                bf16_t* __restrict__ out, int64_t ldo) {
+  // two V blocks per wave; after the loop the waves' partial results
+  __shared__ __attribute__((aligned(1024))) char smem[ATT_S_WAVES * 2 * ATT_S_VBUF];
+  __shared__ float part_m[ATT_S_WAVES][32], part_l[ATT_S_WAVES][32];
+  const int tid = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave), lane = tid % kWave;
+  const int l32 = lane & 31, hi = lane >> 5, g16 = lane >> 4, i16 = lane & 15;
+  const int head = blockIdx.y, q0 = blockIdx.x * 32;
+  const int64_t hoff = static_cast<int64_t>(head) * ATT_DH;
+  const bf16_t* kh = k + hoff;
+  const bf16_t* vh = v + hoff;
+  const uint32_t ldkv2 = static_cast<uint32_t>(ldkv) * 2u;
+
+  bf16x8 qf[8];
+  {
+    int qr = q0 + l32;
+    qr = qr < Mq ? qr : Mq - 1;
+    const bf16_t* src = q + static_cast<int64_t>(qr) * ldq + hoff + 8 * hi;
+#pragma unroll
+    for (int s = 0; s < 8; ++s) qf[s] = __builtin_bit_cast(bf16x8, ldg16(src + 16 * s));
+  }
+  // V copies: piece m holds rows 4 m .. 4 m + 3 of the block, lane i lands in
+  // row 4 m + i / 16, slot i % 16 (swizzled as in the ring above)
+  const uint32_t v_src = static_cast<uint32_t>((2 * v_block(g16, i16 >> 1) + (i16 & 1)) * 16);
+  const uint32_t vbuf = lds_offset(smem) + wave * 2 * ATT_S_VBUF;
+  bf16x8 kf[8], kn[8];
+  const int krow = perm23(l32);
+  auto issue = [&](int key0, int buf) __attribute__((always_inline)) {
+    const bf16_t* vs = vh + static_cast<int64_t>(key0) * ldkv;
+    const uint32_t last = static_cast<uint32_t>(L - 1 - key0) * ldkv2;  // rows past L: row L - 1 again, masked
+#pragma unroll
+    for (int m = 0; m < 8; ++m) {
+      const uint32_t ro = static_cast<uint32_t>(4 * m + g16) * ldkv2;
+      lds_copy16_s(vs, (ro < last ? ro : last) + v_src, vbuf + buf * ATT_S_VBUF + m * 1024);
+    }
+    const int kr = key0 + krow < L ? key0 + krow : L - 1;
+    const bf16_t* ks = kh + static_cast<int64_t>(kr) * ldkv + 8 * hi;
+#pragma unroll
+    for (int s = 0; s < 8; ++s) kn[s] = __builtin_bit_cast(bf16x8, ldg16(ks + 16 * s));
+  };
+  int v_rd[4];  // as in the ring above, within a block
+#pragma unroll
+  for (int d = 0; d < 4; ++d) {
+    const int rlow = 8 * (g16 >> 1) + (i16 >> 2);
+    v_rd[d] = rlow * 256 + v_block(rlow, 2 * d + (g16 & 1)) * 32 + 8 * (i16 & 3);
+  }
+  f32x16 o[4];
+#pragma unroll
+  for (int d = 0; d < 4; ++d)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) o[d][r] = 0.0f;
+  // the reference starts at the lowest finite value, below any score's: a wave
+  // without keys, or with none but -inf scores, merges with weight 0
+  float mc = -3.402823466e38f, l_run = 0.0f;
+  const f32x16 zero16 = {};
+  const bf16x2 ones = {static_cast<__bf16>(1.0f), static_cast<__bf16>(1.0f)};
+  const int nb = (L + 31) / 32;
+  if (wave < nb) issue(wave * 32, 0);
+  for (int b = wave, buf = 0; b < nb; b += ATT_S_WAVES, buf ^= 1) {
+    __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));  // this block's V copies and K fragments
+#pragma unroll
+    for (int s = 0; s < 8; ++s) kf[s] = kn[s];
+    if (b + ATT_S_WAVES < nb) issue((b + ATT_S_WAVES) * 32, buf ^ 1);
+    __builtin_amdgcn_sched_barrier(0);
+    f32x16 sh = zero16;
+#pragma unroll
+    for (int s = 0; s < 8; ++s) sh = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[s], qf[s], sh, 0, 0, 0);
+    if (b * 32 + 32 > L) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        sh[r] = b * 32 + 16 * (r >> 3) + 8 * hi + (r & 7) < L ? sh[r] : -INFINITY;
+    }
+    float mx = sh[0];
+#pragma unroll
+    for (int r = 1; r < 16; ++r) mx = fmaxf(mx, sh[r]);
+    mx = pair_max(mx) * scale_log2;
+    const bool grow = mx - mc > ATT_RESCALE_LOG2;
+    if (__ballot(grow) != 0ull) {
+      const float alpha = grow ? __builtin_amdgcn_exp2f(mc - mx) : 1.0f;
+      mc = grow ? mx : mc;
+      l_run *= alpha;
+#pragma unroll
+      for (int d = 0; d < 4; ++d)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) o[d][r] *= alpha;
+    }
+    bf16x8 pf[2];
+    float psum = 0.0f;
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+      const float t0 = __builtin_amdgcn_exp2f(fmaf(sh[2 * c], scale_log2, -mc));
+      const float t1 = __builtin_amdgcn_exp2f(fmaf(sh[2 * c + 1], scale_log2, -mc));
+      const int a = c / 4, j = 2 * (c % 4);
+      pf[a][j] = static_cast<__bf16>(t0);
+      pf[a][j + 1] = static_cast<__bf16>(t1);
+      const bf16x2 pair = {pf[a][j], pf[a][j + 1]};
+      psum = __builtin_amdgcn_fdot2_f32_bf16(pair, ones, psum, false);
+    }
+    l_run += psum;
+    const char* vs = smem + wave * 2 * ATT_S_VBUF + buf * ATT_S_VBUF;
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int d = 0; d < 4; ++d) {
+        const v4i16 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(ECHO_LDS_V4(vs + a * 16 * 256 + v_rd[d]));
+        const v4i16 up = __builtin_amdgcn_ds_read_tr16_b64_v4i16(ECHO_LDS_V4(vs + a * 16 * 256 + v_rd[d] + 4 * 256));
+        const bf16x8 va = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, up, 0, 1, 2, 3, 4, 5, 6, 7));
+        o[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, pf[a], o[d], 0, 0, 0);
+      }
+  }
+  __syncthreads();  // every wave is done with its V blocks
+  // partial results in the accumulator layout: (d * 16 + r) * 64 + lane
+  float* po = reinterpret_cast<float*>(smem) + wave * (4 * 16 * kWave);
+#pragma unroll
+  for (int d = 0; d < 4; ++d)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) po[(d * 16 + r) * kWave + lane] = o[d][r];
+  const float lsum = pair_sum(l_run);
+  if (hi == 0) {
+    part_m[wave][l32] = mc;
+    part_l[wave][l32] = lsum;
+  }
+  __syncthreads();
+  // a thread takes 8 consecutive outputs (16 bytes) of a query: element j is
+  // register r = 4 (dh / 8 % 4) + j % 4 of lanes j / 4 * 32 + query
+  const int qi = tid % 32, ch = tid / 32;
+  static_assert(ATT_S_WAVES * kWave == 32 * (ATT_DH / 8), "one piece per thread");
+  if (q0 + qi >= Mq) return;
+  float mt = part_m[0][qi];
+#pragma unroll
+  for (int w = 1; w < ATT_S_WAVES; ++w) mt = fmaxf(mt, part_m[w][qi]);
+  float lt = 0.0f, acc[8] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+  for (int w = 0; w < ATT_S_WAVES; ++w) {
+    const float f = __builtin_amdgcn_exp2f(part_m[w][qi] - mt);
+    lt += f * part_l[w][qi];
+    const float* src = reinterpret_cast<const float*>(smem) + w * (4 * 16 * kWave) +
+                       ((ch / 4) * 16 + 4 * (ch % 4)) * kWave + qi;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) acc[j] += f * src[(j % 4) * kWave + (j / 4) * 32];
+  }
+#pragma unroll
+  for (int j = 0; j < 8; ++j) acc[j] /= lt;
+  stg16(out + static_cast<int64_t>(q0 + qi) * ldo + hoff + ch * 8, pack16(acc, static_cast<const bf16_t*>(nullptr)));
+}
+
 constexpr int ATT_MAX_RANGES = 1024;  // ranges of a balanced list
 
 // Merge the fragments of the items of a balanced list: o = sum_s 2^{r_s - r}
@@ -873,37 +1041,93 @@ AttPlan att_plan(int Mq, int L, int H, int ncu) {
   return p;
 }
 
-template <int QB, int WAVES>
-hipError_t launch_attn_variant(const bf16_t* q, int64_t ldq, const bf16_t* k, const bf16_t* v,
-                               int64_t ldkv, int Mq, int L, int H, bf16_t* out, int64_t ldo,
-                               float* part, size_t part_bytes, hipStream_t stream, const char* name) {
-  if (Mq <= 0) return hipSuccess;
-  typedef AttCfg<QB, WAVES> C;
-  const float scale_log2 = static_cast<float>(1.4426950408889634 / sqrt(static_cast<double>(ATT_DH)));
-  const AttPlan plan = att_plan<C::kQ>(Mq, L, H, device_cu_count());
-  ::echo::TimedLaunch scope(name, stream);
-  AttWork whole{};
-  if (!plan.balanced || part == nullptr || part_bytes < plan.bytes) {
-    const int items = AttList(Mq, H, L, C::kQ, whole).items();
-    hipLaunchKernelGGL((attn_fwd_bf16<QB, WAVES>), dim3(items), dim3(C::kThreads), 0, stream, q, ldq, k, v,
-                       ldkv, Mq, L, H, scale_log2, out, ldo, whole, nullptr, nullptr);
-    return hipGetLastError();
+// ---- choice of the kernel and of the queries per workgroup.  Items of 384
+// queries (three waves per SIMD) cost least per query where they fill whole
+// rounds; with less than one round of full items the chip is better filled by
+// items of 256 or 128 queries, by the balanced key ranges, or by the short
+// kernel, whichever is estimated to end first.  Times in microseconds,
+// measured on MI355X (256 CUs) over 21 shapes of 33 .. 13104 queries, 77 ..
+// 32760 keys and 2 .. 40 heads; in order 384 balanced / 384 / 256 / 128 / short:
+//   1950 x 512 x 12      - / 27 / 21 / 17 / 30     4480 x 7800 x 12  208 / 234 / 192 / 253 / 504
+//   600 x 1560 x 12      - / 57 / 42 / 32 / 22     7800 x 7800 x 12  375 / 317 / 372 / 397 / 863
+//   1500 x 2000 x 24    66 / 70 / 51 / 78 / 113    1950 x 7800 x 12  110 / 232 / 159 / 124 / 219
+enum AttKind { ATT_BALANCED, ATT_384, ATT_256, ATT_128, ATT_SHORT };
+
+// whole items of 32 W queries: a round takes c per key tile (less while CUs
+// are idle: the clock is higher) and f beside them
+inline float att_whole_us(int W, int Mq, int L, int H, int ncu) {
+  const int items = H * ((Mq + 32 * W - 1) / (32 * W)), nkt = (L + ATT_KT - 1) / ATT_KT;
+  const float busy = items < ncu ? static_cast<float>(items) / ncu : 1.0f;
+  const float c = W == 12 ? 1.9f + 0.65f * busy : W == 8 ? 1.3f + 0.2f * busy : 0.92f + 0.1f * busy;
+  const float f = W == 12 ? 9.0f : W == 8 ? 6.0f : 6.5f;
+  return 2.0f + static_cast<float>((items + ncu - 1) / ncu) * (nkt * c + f);
+}
+inline float att_short_us(int Mq, int L, int H, int ncu) {
+  const int wgs = H * ((Mq + 31) / 32), blocks = ((L + 31) / 32 + ATT_S_WAVES - 1) / ATT_S_WAVES;
+  return 1.0f + static_cast<float>((wgs + ncu - 1) / ncu) * (blocks * 2.35f + 4.7f);
+}
+
+// any_order: a row's result may depend on the other rows (the kernel and the
+// key ranges change the order of its sums); otherwise always whole items of
+// 384 queries.
+AttKind att_choose(const AttPlan& plan, bool any_order, int Mq, int L, int H, int ncu) {
+  if (!any_order) return ATT_384;
+  if (plan.balanced && plan.A > 0) return ATT_BALANCED;
+  AttKind kind = ATT_384;
+  float us = att_whole_us(12, Mq, L, H, ncu);
+  auto consider = [&](AttKind k, float t) {
+    if (t < us) {
+      kind = k;
+      us = t;
+    }
+  };
+  if (plan.balanced) {
+    // its share of the list's key tiles, two fragments to start and store, the combine
+    const float tiles = static_cast<float>(plan.w.total) / ATT_COST_FULL / plan.G;
+    const int kq = AttCfg<1, 12>::kQ;
+    consider(ATT_BALANCED, tiles * 2.55f * static_cast<float>((plan.G + ncu - 1) / ncu) + 24.0f +
+                               0.08f * static_cast<float>(H * ((Mq + kq - 1) / kq)));
   }
+  if (H * (Mq / AttCfg<1, 12>::kQ) < ncu) {
+    consider(ATT_256, att_whole_us(8, Mq, L, H, ncu));
+    consider(ATT_128, att_whole_us(4, Mq, L, H, ncu));
+    consider(ATT_SHORT, att_short_us(Mq, L, H, ncu));
+  }
+  return kind;
+}
+
+template <int WAVES>
+hipError_t launch_attn_whole(const bf16_t* q, int64_t ldq, const bf16_t* k, const bf16_t* v, int64_t ldkv,
+                             int Mq, int L, int H, float scale_log2, bf16_t* out, int64_t ldo,
+                             hipStream_t stream) {
+  typedef AttCfg<1, WAVES> C;
+  const AttWork whole{};
+  const int items = AttList(Mq, H, L, C::kQ, whole).items();
+  hipLaunchKernelGGL((attn_fwd_bf16<1, WAVES>), dim3(items), dim3(C::kThreads), 0, stream, q, ldq, k, v, ldkv,
+                     Mq, L, H, scale_log2, out, ldo, whole, nullptr, nullptr);
+  return hipGetLastError();
+}
+
+hipError_t launch_attn_balanced(const AttPlan& plan, const bf16_t* q, int64_t ldq, const bf16_t* k, const bf16_t* v,
+                                int64_t ldkv, int Mq, int L, int H, float scale_log2, bf16_t* out, int64_t ldo,
+                                float* part, hipStream_t stream) {
+  typedef AttCfg<1, 12> C;
+  const AttWork whole{};
   if (plan.A > 0) {
-    hipLaunchKernelGGL((attn_fwd_bf16<QB, WAVES>), dim3(plan.A), dim3(C::kThreads), 0, stream, q, ldq, k, v,
-                       ldkv, Mq, L, H, scale_log2, out, ldo, whole, nullptr, nullptr);
+    hipLaunchKernelGGL((attn_fwd_bf16<1, 12>), dim3(plan.A), dim3(C::kThreads), 0, stream, q, ldq, k, v, ldkv, Mq,
+                       L, H, scale_log2, out, ldo, whole, nullptr, nullptr);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
   float* part_o = part;
   float* part_ml = part + static_cast<size_t>(plan.G) * 2 * C::kQ * ATT_DH;
-  hipLaunchKernelGGL((attn_fwd_bf16<QB, WAVES>), dim3(plan.G), dim3(C::kThreads), 0, stream, q, ldq, k,
-                     v, ldkv, Mq, L, H, scale_log2, out, ldo, plan.w, part_o, part_ml);
-  hipError_t e = hipGetLastError();
+  hipLaunchKernelGGL((attn_fwd_bf16<1, 12>), dim3(plan.G), dim3(C::kThreads), 0, stream, q, ldq, k, v, ldkv, Mq, L,
+                     H, scale_log2, out, ldo, plan.w, part_o, part_ml);
+  const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const int rest = AttList(Mq, H, L, C::kQ, whole).items() - plan.A;
-  hipLaunchKernelGGL((attn_combine<QB, WAVES>), dim3(static_cast<unsigned>(rest * (C::kQ / 32))), dim3(256), 0,
-                     stream, part_o, part_ml, plan.w, plan.G, Mq, L, H, out, ldo);
+  hipLaunchKernelGGL((attn_combine<1, 12>), dim3(static_cast<unsigned>(rest * (C::kQ / 32))), dim3(256), 0, stream,
+                     part_o, part_ml, plan.w, plan.G, Mq, L, H, out, ldo);
   return hipGetLastError();
 }
 
@@ -922,8 +1146,26 @@ size_t attn_partial_bytes(int Mq_max, int L, int H) {
 hipError_t launch_attn_bf16(const bf16_t* q, int64_t ldq, const bf16_t* k, const bf16_t* v,
                             int64_t ldkv, int Mq, int L, int H, bf16_t* out, int64_t ldo,
                             float* part, size_t part_bytes, hipStream_t stream, const char* timing_name) {
-  return launch_attn_variant<1, 12>(q, ldq, k, v, ldkv, Mq, L, H, out, ldo, part, part_bytes, stream,
-                                   timing_name);
+  if (Mq <= 0) return hipSuccess;
+  const float scale_log2 = static_cast<float>(1.4426950408889634 / sqrt(static_cast<double>(ATT_DH)));
+  const int ncu = device_cu_count();
+  AttPlan plan = att_plan<AttCfg<1, 12>::kQ>(Mq, L, H, ncu);
+  if (part_bytes < plan.bytes) plan.balanced = false;
+  ::echo::TimedLaunch scope(timing_name, stream);
+  switch (att_choose(plan, part != nullptr, Mq, L, H, ncu)) {
+    case ATT_BALANCED:
+      return launch_attn_balanced(plan, q, ldq, k, v, ldkv, Mq, L, H, scale_log2, out, ldo, part, stream);
+    case ATT_256:
+      return launch_attn_whole<8>(q, ldq, k, v, ldkv, Mq, L, H, scale_log2, out, ldo, stream);
+    case ATT_128:
+      return launch_attn_whole<4>(q, ldq, k, v, ldkv, Mq, L, H, scale_log2, out, ldo, stream);
+    case ATT_SHORT:
+      hipLaunchKernelGGL(attn_short_bf16, dim3((Mq + 31) / 32, H), dim3(ATT_S_WAVES * 64), 0, stream, q, ldq, k, v,
+                         ldkv, Mq, L, scale_log2, out, ldo);
+      return hipGetLastError();
+    default:
+      return launch_attn_whole<12>(q, ldq, k, v, ldkv, Mq, L, H, scale_log2, out, ldo, stream);
+  }
 }
 
 }  // namespace echo

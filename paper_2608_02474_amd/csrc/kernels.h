@@ -125,8 +125,9 @@ hipError_t launch_gemm_f32(const char* name, int epi, const GemmF32Args& a, hipS
 
 // `part` (part_bytes; attn_partial_bytes(Mq_max, L, H) is enough for any Mq
 // up to Mq_max) holds the partial results of the key-range pieces that
-// balance the last round; with part == nullptr, or less room, every work item
-// runs whole.
+// balance the last round; with less room no item is cut.  With part == nullptr
+// every work item also has the same size and kernel whatever Mq is, so that a
+// row's result does not depend on the other rows.
 hipError_t launch_attn_bf16(const bf16_t* q, int64_t ldq, const bf16_t* k, const bf16_t* v,
                             int64_t ldkv, int Mq, int L, int H, bf16_t* out, int64_t ldo,
                             float* part, size_t part_bytes, hipStream_t stream,

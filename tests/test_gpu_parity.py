@@ -364,6 +364,44 @@ def test_block_partial_f32_edges(w):
         assert torch.equal(ys, full[torch.from_numpy(idx.astype(np.int64)).to(full.device)]), n
 
 
+# shapes whose attention runs items of 128 and of 256 queries (its other kernels run in the blocks above)
+ITEMS = [
+    synth.Workload("items128_bf16_400tok", T=4, grid=(10, 10), D=2560, H=20, F=512, n_samples=4000, ratio=0.5,
+                   dtype="bf16", audio="speech", seed=81),
+    synth.Workload("items256_bf16_1700tok", T=5, grid=(17, 20), D=2560, H=20, F=512, n_samples=4000, ratio=0.5,
+                   dtype="bf16", audio="speech", seed=82),
+]
+
+
+@pytest.mark.parametrize("w", ITEMS, ids=lambda w: w.name)
+def test_block_partial_attention_items(w):
+    p = synth.make_block_weights(w)
+    _, x = synth.make_latents(w)
+    rng = np.random.default_rng(14)
+    kv = OB.kv_projection(OB._f64(p), np.asarray(x, np.float64))
+    for n in (w.L - 1, w.L):
+        idx = np.sort(rng.choice(w.L, n, replace=False))
+        rows = np.unique(np.r_[0, n - 1, np.arange(0, n, 29), n - n % 128 - 1])
+        say(f"block {w.name} n={n}")
+        got = _block_gpu(w, p, x, idx)[rows]
+        check_block(got, OB.block_partial(p, x, idx[rows], w.H, kv=kv), w.dtype, f"{w.name}/n={n}")
+
+
+def test_block_partial_attention_rescale_few_keys():
+    """The rescale case below on the kernel for few queries and keys, whose
+    waves each keep a reference of their own: 700 keys, so that a wave holds up
+    to three 32-key blocks and the last block is ragged."""
+    w = synth.Workload("rescale_bf16_700tok", T=5, grid=(10, 14), D=256, H=2, F=512,
+                       n_samples=4000, ratio=0.5, dtype="bf16", audio="bursts", seed=78)
+    p = synth.make_block_weights(w)
+    for name in ("wq", "wk"):
+        p[name] = synth.storage_round(p[name] * 10.0, w.dtype)
+    _, x = synth.make_latents(w)
+    kv = OB.kv_projection(OB._f64(p), np.asarray(x, np.float64))
+    idx = np.sort(np.random.default_rng(15).choice(w.L, 200, replace=False))
+    check_block(_block_gpu(w, p, x, idx), OB.block_partial(p, x, idx, w.H, kv=kv), w.dtype, "rescale, few keys")
+
+
 def _reference_moves(q, k, H):
     """Per (query, head) row: how often a lazily rescaled streaming softmax
     moves its reference over the keys in 32-key halves (the reference starts
