@@ -33,14 +33,21 @@ __device__ __forceinline__ float gelu_tanh_ref(float z) {
 // see launch_gemm_f32.  32 tokens, 16 selected, D 64, F 256 (depths 64 and 256):
 // 3.9 - 9.6 us per product with 16 x 16 tiles staged through LDS -> 3.1 - 3.6;
 // 600 tokens, 400 selected, D 512, F 1024: the whole step 576 -> 117 us.
+// The grid's third dimension picks one of two products (the second may have
+// fewer or more tiles than the first: workgroups past a product's end leave).
+struct GemmF32Pair {
+  GemmF32Args g[2];
+};
 template <int EPI, int T>  // 0 bias, 1 gelu, 2 gate+residual (same codes as the bf16 GEMM)
-__global__ void __launch_bounds__(F32_WAVES * kWave) gemm_f32_nt(GemmF32Args p) {
+__global__ void __launch_bounds__(F32_WAVES * kWave) gemm_f32_nt(GemmF32Pair pair) {
+  const GemmF32Args& p = pair.g[blockIdx.z];
   constexpr int TILE = 16 * T, LD = TILE + 1;
   constexpr int UNR = T == 1 ? 4 : 2;  // chunks whose loads are in flight together
   __shared__ float part[F32_WAVES][TILE * LD];
   const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
   const int l16 = lane & 15, lq = lane >> 4;
   const int m0 = blockIdx.y * TILE, n0 = blockIdx.x * TILE;
+  if (m0 >= p.M || n0 >= p.N) return;  // uniform
   const float* arow[T];
   const float* brow[T];
 #pragma unroll
@@ -259,23 +266,38 @@ attn_fwd_f32(const float* __restrict__ q, int64_t ldq, const float* __restrict__
 }
 
 template <int T>
-static hipError_t launch_gemm_f32_t(const char* name, int epi, const GemmF32Args& a, hipStream_t stream) {
-  const dim3 grid((a.N + 16 * T - 1) / (16 * T), (a.M + 16 * T - 1) / (16 * T));
+static hipError_t launch_gemm_f32_t(const char* name, int epi, const GemmF32Pair& p, int count, hipStream_t stream) {
+  int M = p.g[0].M, N = p.g[0].N;
+  if (count > 1) {
+    M = p.g[1].M > M ? p.g[1].M : M;
+    N = p.g[1].N > N ? p.g[1].N : N;
+  }
+  const dim3 grid((N + 16 * T - 1) / (16 * T), (M + 16 * T - 1) / (16 * T), count);
   const dim3 block(F32_WAVES * kWave);
   switch (epi) {
-    case 0: return ECHO_LAUNCH(name, (gemm_f32_nt<0, T>), grid, block, 0, stream, a);
-    case 1: return ECHO_LAUNCH(name, (gemm_f32_nt<1, T>), grid, block, 0, stream, a);
-    default: return ECHO_LAUNCH(name, (gemm_f32_nt<2, T>), grid, block, 0, stream, a);
+    case 0: return ECHO_LAUNCH(name, (gemm_f32_nt<0, T>), grid, block, 0, stream, p);
+    case 1: return ECHO_LAUNCH(name, (gemm_f32_nt<1, T>), grid, block, 0, stream, p);
+    default: return ECHO_LAUNCH(name, (gemm_f32_nt<2, T>), grid, block, 0, stream, p);
   }
+}
+
+static int64_t f32_tiles(const GemmF32Args& a) {
+  return static_cast<int64_t>((a.M + 31) / 32) * ((a.N + 31) / 32);
 }
 
 hipError_t launch_gemm_f32(const char* name, int epi, const GemmF32Args& a, hipStream_t stream) {
   if (a.M <= 0) return hipSuccess;
   // 32 x 32 tiles once they are two to a CU (below that the 16 x 16 ones, four
   // times as many, finish sooner)
-  const int64_t tiles = static_cast<int64_t>((a.M + 31) / 32) * ((a.N + 31) / 32);
-  return tiles >= 2 * device_cu_count() ? launch_gemm_f32_t<2>(name, epi, a, stream)
-                                        : launch_gemm_f32_t<1>(name, epi, a, stream);
+  const GemmF32Pair p{{a, a}};
+  return f32_tiles(a) >= 2 * device_cu_count() ? launch_gemm_f32_t<2>(name, epi, p, 1, stream)
+                                               : launch_gemm_f32_t<1>(name, epi, p, 1, stream);
+}
+
+hipError_t launch_gemm_f32_pair(const char* name, const GemmF32Args& a, const GemmF32Args& b, hipStream_t stream) {
+  const GemmF32Pair p{{a, b}};
+  return f32_tiles(a) + f32_tiles(b) >= 2 * device_cu_count() ? launch_gemm_f32_t<2>(name, 0, p, 2, stream)
+                                                              : launch_gemm_f32_t<1>(name, 0, p, 2, stream);
 }
 
 hipError_t launch_attn_f32(const float* q, int64_t ldq, const float* k, const float* v, int64_t ldkv,

@@ -497,15 +497,16 @@ int echo_block_partial(const echo_block_cfg* cfg, const echo_block_weights* w, c
       return a;
     };
     // q = a[idx] Wq^T + bq
-    g = GemmBf16Args{static_cast<P>(ws.a), D, idx, L, static_cast<P>(w->wq), static_cast<P>(w->wq), D, D,
-                     static_cast<P>(w->bq), static_cast<P>(w->bq), n, D, D, ws.q, D,
-                     nullptr, nullptr, 0, nullptr, 0};
-    if ((e = launch_gemm_bf16("gemm_q_bf16", 0, with_part(g), st)) != hipSuccess) return device_status(e);
+    const GemmBf16Args gq{static_cast<P>(ws.a), D, idx, L, static_cast<P>(w->wq), static_cast<P>(w->wq), D, D,
+                          static_cast<P>(w->bq), static_cast<P>(w->bq), n, D, D, ws.q, D,
+                          nullptr, nullptr, 0, nullptr, 0};
     // [k | v] = a [Wk; Wv]^T + [bk; bv], one N = 2D GEMM over all L rows
     g = GemmBf16Args{static_cast<P>(ws.a), D, nullptr, L, static_cast<P>(w->wk), static_cast<P>(w->wv), D,
                      D, static_cast<P>(w->bk), static_cast<P>(w->bv), L, 2 * D, D, ws.kv, 2 * D,
                      nullptr, nullptr, 0, nullptr, 0};
-    if ((e = launch_gemm_bf16("gemm_kv_bf16", 0, with_part(g), st)) != hipSuccess) return device_status(e);
+    if ((e = launch_gemm_bf16_pair("gemm_qkv_bf16", "gemm_q_bf16", "gemm_kv_bf16", with_part(gq), with_part(g), st)) !=
+        hipSuccess)
+      return device_status(e);
     const bf16_t* kvp = static_cast<const bf16_t*>(ws.kv);
     if ((e = launch_attn_bf16(static_cast<P>(ws.q), D, kvp, kvp + D, 2 * D, n, L, H,
                               static_cast<bf16_t*>(ws.o), D,
@@ -534,15 +535,13 @@ int echo_block_partial(const echo_block_cfg* cfg, const echo_block_weights* w, c
   }
   typedef const float* P;
   const int dh = D / H;
-  GemmF32Args g{};
-  g = GemmF32Args{static_cast<P>(ws.a), D, idx, static_cast<P>(w->wq), static_cast<P>(w->wq), D, D,
+  const GemmF32Args gq{static_cast<P>(ws.a), D, idx, static_cast<P>(w->wq), static_cast<P>(w->wq), D, D,
                   static_cast<P>(w->bq), static_cast<P>(w->bq), n, D, D, static_cast<float*>(ws.q), D,
                   nullptr, nullptr, 0, nullptr};
-  if ((e = launch_gemm_f32("gemm_q_f32", 0, g, st)) != hipSuccess) return device_status(e);
-  g = GemmF32Args{static_cast<P>(ws.a), D, nullptr, static_cast<P>(w->wk), static_cast<P>(w->wv), D, D,
+  GemmF32Args g{static_cast<P>(ws.a), D, nullptr, static_cast<P>(w->wk), static_cast<P>(w->wv), D, D,
                   static_cast<P>(w->bk), static_cast<P>(w->bv), L, 2 * D, D,
                   static_cast<float*>(ws.kv), 2 * D, nullptr, nullptr, 0, nullptr};
-  if ((e = launch_gemm_f32("gemm_kv_f32", 0, g, st)) != hipSuccess) return device_status(e);
+  if ((e = launch_gemm_f32_pair("gemm_qkv_f32", gq, g, st)) != hipSuccess) return device_status(e);
   const float* kvp = static_cast<const float*>(ws.kv);
   if ((e = launch_attn_f32(static_cast<P>(ws.q), D, kvp, kvp + D, 2 * D, n, L, H, dh,
                            static_cast<float*>(ws.o), D, st)) != hipSuccess)
@@ -607,15 +606,13 @@ int echo_wan_block_partial(const echo_wan_block_cfg* cfg, const echo_wan_block_w
   ECHO_TRY(launch_vec_shift(w->g3, -1.0f, ws.g3m1, D, st));
   // self-attention
   ECHO_TRY(launch_modln_input(1, x, BL, D, mod + 0 * D, mod + 1 * D, cfg->ln_eps, ws.a, st));
-  GemmBf16Args g{};
-  g = GemmBf16Args{static_cast<P>(ws.a), D, idx, BL, static_cast<P>(w->self.wq), static_cast<P>(w->self.wq), D, D,
-                   static_cast<P>(w->self.bq), static_cast<P>(w->self.bq), n, D, D, ws.q, D,
-                   nullptr, nullptr, 0, nullptr, 0};
-  ECHO_TRY(launch_gemm_bf16("gemm_q_bf16", 0, with_part(g), st));
-  g = GemmBf16Args{static_cast<P>(ws.a), D, nullptr, BL, static_cast<P>(w->self.wk), static_cast<P>(w->self.wv), D,
+  const GemmBf16Args gq{static_cast<P>(ws.a), D, idx, BL, static_cast<P>(w->self.wq), static_cast<P>(w->self.wq), D, D,
+                        static_cast<P>(w->self.bq), static_cast<P>(w->self.bq), n, D, D, ws.q, D,
+                        nullptr, nullptr, 0, nullptr, 0};
+  GemmBf16Args g{static_cast<P>(ws.a), D, nullptr, BL, static_cast<P>(w->self.wk), static_cast<P>(w->self.wv), D,
                    D, static_cast<P>(w->self.bk), static_cast<P>(w->self.bv), BL, 2 * D, D, ws.kv, 2 * D,
                    nullptr, nullptr, 0, nullptr, 0};
-  ECHO_TRY(launch_gemm_bf16("gemm_kv_bf16", 0, with_part(g), st));
+  ECHO_TRY(launch_gemm_bf16_pair("gemm_qkv_bf16", "gemm_q_bf16", "gemm_kv_bf16", with_part(gq), with_part(g), st));
   ECHO_TRY(launch_qk_norm_rope(static_cast<bf16_t*>(ws.q), D, n, D, w->gq, cfg->rms_eps, idx, ws.tab, L, cfg->T,
                                cfg->gh, cfg->gw, dh, st));
   ECHO_TRY(launch_qk_norm_rope(static_cast<bf16_t*>(ws.kv), 2 * D, BL, D, w->gk, cfg->rms_eps, nullptr, ws.tab, L,
@@ -636,14 +633,13 @@ int echo_wan_block_partial(const echo_wan_block_cfg* cfg, const echo_wan_block_w
   ECHO_TRY(launch_gemm_bf16("gemm_o_bf16", 2, with_part(g), st));
   // cross-attention: c = LN(x1) * g3 + b3 = LN(x1) * (1 + (g3 - 1)) + b3
   ECHO_TRY(launch_modln_x1(1, ws.x1, n, D, w->b3, ws.g3m1, cfg->ln_eps, ws.b, st));
-  g = GemmBf16Args{static_cast<P>(ws.b), D, nullptr, n, static_cast<P>(w->wqc), static_cast<P>(w->wqc), D, D,
-                   static_cast<P>(w->bqc), static_cast<P>(w->bqc), n, D, D, ws.q, D,
-                   nullptr, nullptr, 0, nullptr, 0};
-  ECHO_TRY(launch_gemm_bf16("gemm_qc_bf16", 0, with_part(g), st));
+  const GemmBf16Args gqc{static_cast<P>(ws.b), D, nullptr, n, static_cast<P>(w->wqc), static_cast<P>(w->wqc), D, D,
+                         static_cast<P>(w->bqc), static_cast<P>(w->bqc), n, D, D, ws.q, D,
+                         nullptr, nullptr, 0, nullptr, 0};
   g = GemmBf16Args{static_cast<P>(ctx), D, nullptr, BLc, static_cast<P>(w->wkc), static_cast<P>(w->wvc), D, D,
                    static_cast<P>(w->bkc), static_cast<P>(w->bvc), BLc, 2 * D, D, ws.kvc, 2 * D,
                    nullptr, nullptr, 0, nullptr, 0};
-  ECHO_TRY(launch_gemm_bf16("gemm_kvc_bf16", 0, with_part(g), st));
+  ECHO_TRY(launch_gemm_bf16_pair("gemm_qkvc_bf16", "gemm_qc_bf16", "gemm_kvc_bf16", with_part(gqc), with_part(g), st));
   ECHO_TRY(launch_qk_norm_rope(static_cast<bf16_t*>(ws.q), D, n, D, w->gqc, cfg->rms_eps, nullptr, nullptr, L,
                                cfg->T, cfg->gh, cfg->gw, dh, st));
   ECHO_TRY(launch_qk_norm_rope(static_cast<bf16_t*>(ws.kvc), 2 * D, BLc, D, w->gkc, cfg->rms_eps, nullptr, nullptr,

@@ -477,14 +477,13 @@ struct SmCfg {
   static constexpr int kWgPerCu = kLds <= 53 * 1024 ? 3 : kLds <= 80 * 1024 ? 2 : 1;
 };
 
+// (workgroup `block` of the `nblocks` of product p)
 template <int BM, int BN, int KG, int EPI>
-__global__ void __launch_bounds__(256 * KG, (SmCfg<BM, BN, KG>::kWgPerCu * KG))
-gemm_bf16_sm(GemmBf16Args p) {
+__device__ __forceinline__ void gemm_sm_tile(const GemmBf16Args& p, int block, int nblocks, char* smem) {
   typedef SmCfg<BM, BN, KG> C;
   constexpr int WM = BM / 2, WN = BN / 2, TI = WM / 16, TJ = WN / 16;
   constexpr int NM = TI * TJ, NR = TI + TJ;                 // MFMAs and fragment reads of a k32 half
   constexpr int CA = BM / 32, CB = BN / 32, NCP = CA + CB;  // copies per wave and k-step
-  __shared__ __attribute__((aligned(1024))) char smem[C::kLds];
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave), lane = tid % kWave;
   const int grp = wave / 4, w4 = wave % 4;
@@ -494,8 +493,8 @@ gemm_bf16_sm(GemmBf16Args p) {
   // ---- tile and k-range: XCD x takes a contiguous range of the grouped order
   // (with nsplit > 1, of the pieces: the k-ranges of a tile are neighbours)
   const int tm = (p.M + BM - 1) / BM, tn = p.N / BN;
-  const int per = gridDim.x / 8, rem = gridDim.x % 8, xcd = blockIdx.x % 8;
-  const int piece = xcd * per + (xcd < rem ? xcd : rem) + blockIdx.x / 8;
+  const int per = nblocks / 8, rem = nblocks % 8, xcd = block % 8;
+  const int piece = xcd * per + (xcd < rem ? xcd : rem) + block / 8;
   const bool split_k = p.nsplit > 1;
   const int pid = split_k ? piece / p.nsplit : piece;
   int tile_m, tile_n;
@@ -693,6 +692,28 @@ gemm_bf16_sm(GemmBf16Args p) {
   }
 }
 
+template <int BM, int BN, int KG, int EPI>
+__global__ void __launch_bounds__(256 * KG, (SmCfg<BM, BN, KG>::kWgPerCu * KG))
+gemm_bf16_sm(GemmBf16Args p) {
+  __shared__ __attribute__((aligned(1024))) char smem[SmCfg<BM, BN, KG>::kLds];
+  gemm_sm_tile<BM, BN, KG, EPI>(p, blockIdx.x, gridDim.x, smem);
+}
+
+// Two products of the same tile in one launch: workgroups [0, na) work on a,
+// the rest on b.
+struct GemmBf16Pair {
+  GemmBf16Args a, b;
+  int na;
+};
+template <int BM, int BN, int KG, int EPI>
+__global__ void __launch_bounds__(256 * KG, (SmCfg<BM, BN, KG>::kWgPerCu * KG))
+gemm_bf16_sm_pair(GemmBf16Pair p) {
+  __shared__ __attribute__((aligned(1024))) char smem[SmCfg<BM, BN, KG>::kLds];
+  const bool first = static_cast<int>(blockIdx.x) < p.na;  // uniform: one copy of the code, its operands chosen
+  const GemmBf16Args& g = first ? p.a : p.b;
+  gemm_sm_tile<BM, BN, KG, EPI>(g, first ? blockIdx.x : blockIdx.x - p.na, first ? p.na : gridDim.x - p.na, smem);
+}
+
 // Sum the k-range partials of the split tail tiles in split order and apply
 // the epilogue.  One thread per 4 output columns.
 template <int BM, int BN, int EPI>
@@ -773,11 +794,12 @@ float big_us(int tiles, int nk, int ncu, int nsplit) {
   return us;
 }
 
-// Smaller tiles: n workgroups fall to the busiest CU, two (128 x 128) or three
-// (the others) at a time.
-float small_us(GemmTile t, int M, int N, int nk, int nsplit, int ncu) {
-  const int bm = t == TILE_32x64_K2 ? 32 : t == TILE_64 ? 64 : 128, bn = t == TILE_64 || t == TILE_32x64_K2 ? 64 : 128;
-  const int pieces = ((M + bm - 1) / bm) * (N / bn) * nsplit;
+// Smaller tiles: `pieces` workgroups, n on the busiest CU, two (128 x 128) or
+// three (the others) at a time.
+inline int tile_rows(GemmTile t) { return t == TILE_32x64_K2 ? 32 : t == TILE_64 ? 64 : 128; }
+inline int tile_cols(GemmTile t) { return t == TILE_64 || t == TILE_32x64_K2 ? 64 : 128; }
+inline int tile_count(GemmTile t, int M, int N) { return ((M + tile_rows(t) - 1) / tile_rows(t)) * (N / tile_cols(t)); }
+float small_us(GemmTile t, int pieces, int nk, int nsplit, int ncu) {
   const int n = (pieces + ncu - 1) / ncu, steps = (nk + nsplit - 1) / nsplit;
   float us;
   if (t == TILE_128) {
@@ -791,7 +813,8 @@ float small_us(GemmTile t, int M, int N, int nk, int nsplit, int ncu) {
   } else {
     us = 2.3f + 0.5f * (steps + 1) * (0.83f * (n / 3) + (n % 3 == 2 ? 0.45f : n % 3 == 1 ? 0.27f : 0.0f));
   }
-  if (nsplit > 1) us += 3.0f + 0.2e-6f * (static_cast<float>(pieces) * bm * bn * 4.0f);  // partial sums, reduce
+  // partial sums, reduce
+  if (nsplit > 1) us += 3.0f + 0.2e-6f * (static_cast<float>(pieces) * tile_rows(t) * tile_cols(t) * 4.0f);
   return us;
 }
 
@@ -803,7 +826,7 @@ GemmPlan gemm_plan(int M, int N, int K, int ncu, size_t part_bytes) {
   const int nsplit = any_order ? big_tail_split(tiles, nk, ncu, part_bytes) : 1;
   GemmPlan best{TILE_256, nsplit, big_us(tiles, nk, ncu, nsplit)};
   auto consider = [&](GemmTile t, int sp) {
-    const float us = small_us(t, M, N, nk, sp, ncu);
+    const float us = small_us(t, tile_count(t, M, N) * sp, nk, sp, ncu);
     if (us < best.us) best = GemmPlan{t, sp, us};
   };
   consider(TILE_128, 1);
@@ -837,8 +860,10 @@ hipError_t launch_gemm_sm(GemmBf16Args a, int nsplit, hipStream_t stream) {
   hipLaunchKernelGGL((gemm_bf16_sm<BM, BN, KG, EPI>), dim3(tiles * a.nsplit), dim3(SmCfg<BM, BN, KG>::kThreads), 0,
                      stream, a);
   const hipError_t e = hipGetLastError();
-  if (e != hipSuccess || a.nsplit < 2) return e;
-  return launch_splitk_reduce<BM, BN, EPI>(a, tiles, stream);
+  if constexpr (BM == 128 && KG == 1) {  // the only tile whose plans are split
+    if (e == hipSuccess && a.nsplit > 1) return launch_splitk_reduce<BM, BN, EPI>(a, tiles, stream);
+  }
+  return e;
 }
 
 // `a` in 256 x 256 tiles, those of the last partly filled round in nsplit k-ranges
@@ -883,19 +908,63 @@ hipError_t launch_gemm_epi(const char* name, const GemmBf16Args& a, hipStream_t 
   }
 }
 
-hipError_t launch_gemm_bf16(const char* name, int epi, const GemmBf16Args& a, hipStream_t stream) {
-  if (a.M <= 0) return hipSuccess;
+// operands that the tile kernels can address and divide into tiles
+bool gemm_bf16_ok(const GemmBf16Args& a) {
   // the tile loads address A and B through 32-bit byte offsets
   const int64_t lim = int64_t(1) << 31;
-  if (a.a_nrows <= 0 || a.a_nrows * a.lda * 2 >= lim || int64_t(a.N) * a.ldb * 2 >= lim)
-    return hipErrorInvalidValue;
-  if (a.N % kBigTile != 0 || (a.n_split < a.N && a.n_split % kBigTile != 0) || a.K % kBK != 0)
-    return hipErrorInvalidValue;
+  return a.a_nrows > 0 && a.a_nrows * a.lda * 2 < lim && int64_t(a.N) * a.ldb * 2 < lim && a.N % kBigTile == 0 &&
+         (a.n_split >= a.N || a.n_split % kBigTile == 0) && a.K % kBK == 0;
+}
+
+hipError_t launch_gemm_bf16(const char* name, int epi, const GemmBf16Args& a, hipStream_t stream) {
+  if (a.M <= 0) return hipSuccess;
+  if (!gemm_bf16_ok(a)) return hipErrorInvalidValue;
   switch (epi) {
     case EPI_BIAS: return launch_gemm_epi<EPI_BIAS>(name, a, stream);
     case EPI_GELU: return launch_gemm_epi<EPI_GELU>(name, a, stream);
     default: return launch_gemm_epi<EPI_GATE_RES>(name, a, stream);
   }
+}
+
+template <int BM, int BN, int KG>
+hipError_t launch_gemm_sm_pair(const GemmBf16Args& a, const GemmBf16Args& b, hipStream_t stream) {
+  GemmBf16Pair p{a, b, ((a.M + BM - 1) / BM) * (a.N / BN)};
+  p.a.nsplit = p.b.nsplit = 1;
+  const int nb = ((b.M + BM - 1) / BM) * (b.N / BN);
+  hipLaunchKernelGGL((gemm_bf16_sm_pair<BM, BN, KG, EPI_BIAS>), dim3(p.na + nb), dim3(SmCfg<BM, BN, KG>::kThreads), 0,
+                     stream, p);
+  return hipGetLastError();
+}
+
+// One launch where a tile of the smaller kind does both in less than their two
+// own plans take: always for a few hundred rows, where a launch costs as much
+// as its work (300 tokens of width 256, Q and K/V: 4.1 + 3.6 us -> 4.3),
+// and where one's last round leaves room for the other.
+hipError_t launch_gemm_bf16_pair(const char* pair_name, const char* name_a, const char* name_b,
+                                 const GemmBf16Args& a, const GemmBf16Args& b, hipStream_t stream) {
+  if (a.M > 0 && b.M > 0 && a.K == b.K && gemm_bf16_ok(a) && gemm_bf16_ok(b)) {
+    const int ncu = device_cu_count(), nk = a.K / kBK;
+    const bool any_order = a.part != nullptr;
+    const GemmPlan pa = gemm_plan(a.M, a.N, a.K, ncu, any_order ? a.part_bytes : 0);
+    const GemmPlan pb = gemm_plan(b.M, b.N, b.K, ncu, any_order ? b.part_bytes : 0);
+    GemmPlan best{TILE_256, 1, pa.us + pb.us};  // TILE_256: separate launches
+    const GemmTile tiles[] = {TILE_64, TILE_128, TILE_32x64_K2, TILE_128_K2};
+    for (int i = 0; i < (any_order && nk % 2 == 0 ? 4 : 2); ++i) {
+      const float us = small_us(tiles[i], tile_count(tiles[i], a.M, a.N) + tile_count(tiles[i], b.M, b.N), nk, 1, ncu);
+      if (us < best.us) best = GemmPlan{tiles[i], 1, us};
+    }
+    if (best.tile != TILE_256) {
+      ::echo::TimedLaunch scope(pair_name, stream);
+      switch (best.tile) {
+        case TILE_64: return launch_gemm_sm_pair<64, 64, 1>(a, b, stream);
+        case TILE_128: return launch_gemm_sm_pair<128, 128, 1>(a, b, stream);
+        case TILE_128_K2: return launch_gemm_sm_pair<128, 128, 2>(a, b, stream);
+        default: return launch_gemm_sm_pair<32, 64, 2>(a, b, stream);
+      }
+    }
+  }
+  const hipError_t e = launch_gemm_bf16(name_a, EPI_BIAS, a, stream);
+  return e != hipSuccess ? e : launch_gemm_bf16(name_b, EPI_BIAS, b, stream);
 }
 
 }  // namespace echo

@@ -121,7 +121,12 @@ hipError_t launch_modln_x1(int dtype_bf16, const float* x1, int M, int D, const 
                            const float* scale, float eps, void* out, hipStream_t stream);
 
 hipError_t launch_gemm_bf16(const char* name, int epi, const GemmBf16Args& a, hipStream_t stream);
+// two products of the same depth with EPI_BIAS, in one launch where that is faster
+hipError_t launch_gemm_bf16_pair(const char* pair_name, const char* name_a, const char* name_b,
+                                 const GemmBf16Args& a, const GemmBf16Args& b, hipStream_t stream);
 hipError_t launch_gemm_f32(const char* name, int epi, const GemmF32Args& a, hipStream_t stream);
+// two products with epilogue 0 in one launch
+hipError_t launch_gemm_f32_pair(const char* name, const GemmF32Args& a, const GemmF32Args& b, hipStream_t stream);
 
 // `part` (part_bytes; attn_partial_bytes(Mq_max, L, H) is enough for any Mq
 // up to Mq_max) holds the partial results of the key-range pieces that

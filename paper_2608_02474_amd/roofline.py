@@ -28,6 +28,8 @@ def kernel_work(L: int, K: int, D: int, F: int, b: int, n_samples: int = 0):
         "select_segments": (4 * L + 4 * K + L, "byte"),
         # LN1 over all rows: read x, write a
         "modln_in": (2 * L * D * b, "byte"),
+        # the Q and K/V projections in one launch (small blocks), or each in its own
+        "gemm_qkv": (2 * K * D * D + 4 * L * D * D, "flop"),
         "gemm_q": (2 * K * D * D, "flop"),
         "gemm_kv": (4 * L * D * D, "flop"),
         "attn_fwd": (4 * K * L * D, "flop"),
@@ -71,10 +73,12 @@ def wan_block_work(B: int, L: int, K: int, D: int, F: int, Lc: int, b: int):
     norm_bytes = (2 * n + B * L + B * Lc) * D * 2 * b // 4
     return {
         "qk_norm_rope": (norm_bytes, "byte"),
+        "gemm_qkvc": (2 * n * D * D + 4 * B * Lc * D * D, "flop"),
         "gemm_qc": (2 * n * D * D, "flop"),
         "gemm_kvc": (4 * B * Lc * D * D, "flop"),
         "gemm_oc": (2 * n * D * D, "flop"),
         "attn_cross": (4 * K * Lc * D, "flop"),
+        "gemm_qkv": (2 * n * D * D + 4 * B * L * D * D, "flop"),
         "gemm_q": (2 * n * D * D, "flop"),
         "gemm_kv": (4 * B * L * D * D, "flop"),
         "attn_fwd": (4 * K * L * D, "flop"),
