@@ -6,22 +6,30 @@
 //   used) and accumulates
 //   |x - xref| and |xref| in fp64 (exact per-element differences, so only the
 //   summation order differs from the definition).
-//   Writes s_i = fp32(w_frame * num / (den + xi)) plus num/den for the step sum.
-// step_delta_sum: step-level Eq. 1 sum in a fixed order (deterministic); in
-//   echo_select the same sum runs as a second workgroup of select_rows.
+//   Writes s_i = fp32(w_frame * num / (den + xi)) plus, per workgroup of four
+//   rows, the sums of num and of den for the step-level value.
+// step_delta_sum: step-level Eq. 1 sum of those in a fixed order
+//   (deterministic); in echo_select the same sum runs as a second workgroup of
+//   select_rows.
 // select_rows: one 1024-thread workgroup, the keys held in registers
-//   (1) top-K threshold key by 4-pass 8-bit radix select over order-preserving
-//       uint32 keys (histograms in LDS);
+//   (1) top-K threshold key by a radix select over order-preserving uint32
+//       keys in digits of 11, 11 and 10 bits (histograms in LDS);
 //   (2) stable compaction in index order: per (1024-key round, wave) counts,
-//       two block-wide exclusive scans (ranks of equal keys, output slots),
-//       then wave ballot + popcount within each wave; ties at the threshold
-//       key go to the lowest indices.
+//       one block-wide exclusive scan, then the lane's place within each wave
+//       from ballots; ties at the threshold key go to the lowest indices.
 // The key set is tiny (4 bytes per token, L2-resident), so one workgroup keeps
-// the selection exact and deterministic at a cost of a few microseconds.
+// the selection exact and deterministic.  One CU's issue rate is what bounds it:
+// 32760 keys are 32 per thread and every instruction per key costs 0.2 us, so the
+// passes are kept to a few (a shift and an LDS add in the first, a subtract and a
+// compare for the keys outside the digit in the others; a wave's counts in its lanes).
+// Four passes of 8 bits with a leader election per 64 keys and a count written
+// per (round, wave) took 36.5 us at 32760 keys, this form 24.7; 75600 keys 150 -> 67.
 // select_segments: the same selection per anchor segment, one workgroup per
 //   segment (the two-stage form: anchor segments, then min(k, N) tokens each).
 // anchor_select: the anchor segments (top-k of per-segment keys, or evenly
 //   spaced), one workgroup.
+#include <type_traits>
+
 #include "common.h"
 #include "kernels.h"
 #include "launch.h"
@@ -39,9 +47,10 @@ __global__ void __launch_bounds__(kSalThreads)
 saliency_rows(const T* __restrict__ x, const T* __restrict__ xref, const float* __restrict__ fw,
               int L, int N, int D, double xi, float* __restrict__ s_out,
               double* __restrict__ num_out, double* __restrict__ den_out) {
+  __shared__ double part[2][kSalThreads / kWave];
   const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
-  const int64_t row = static_cast<int64_t>(blockIdx.x) * (kSalThreads / kWave) + wave;
-  if (row >= L) return;
+  const int64_t row0 = static_cast<int64_t>(blockIdx.x) * (kSalThreads / kWave) + wave;
+  const int64_t row = row0 < L ? row0 : L - 1;  // past the end: the last row again, not counted
   const T* xr = x + row * D;
   const T* rr = xref + row * D;
   const int nch = D / 8;
@@ -81,26 +90,38 @@ saliency_rows(const T* __restrict__ x, const T* __restrict__ xref, const float* 
   num = wave_sum(num);
   den = wave_sum(den);
   if (lane == 0) {
-    const double delta = num / (den + xi);
-    const double w = static_cast<double>(fw[row / N]);
-    s_out[row] = __double2float_rn(w * delta);
-    num_out[row] = num;
-    den_out[row] = den;
+    if (row0 < L) {
+      const double delta = num / (den + xi);
+      const double w = static_cast<double>(fw[row / N]);
+      s_out[row] = __double2float_rn(w * delta);
+    }
+    part[0][wave] = row0 < L ? num : 0.0;
+    part[1][wave] = row0 < L ? den : 0.0;
+  }
+  __syncthreads();
+  // one pair of sums per workgroup: a quarter of the rows' pairs, which one
+  // workgroup adds up beside the selection
+  if (threadIdx.x < 2) {
+    double t = part[threadIdx.x][0];
+#pragma unroll
+    for (int w = 1; w < kSalThreads / kWave; ++w) t += part[threadIdx.x][w];
+    (threadIdx.x == 0 ? num_out : den_out)[blockIdx.x] = t;
   }
 }
 
 // Step-level Eq. 1 value sum(num) / (sum(den) + xi) in a fixed summation
 // order (deterministic), by one 1024-thread workgroup: its own kernel after a
 // saliency-only call, or the second workgroup of the select_rows launch.
+// num, den: n partial sums.
 __device__ __forceinline__ void step_delta_block(const double* __restrict__ num, const double* __restrict__ den,
-                                                 int L, double xi, double* __restrict__ step_delta) {
+                                                 int n, double xi, double* __restrict__ step_delta) {
   __shared__ double red_n[kSelWaves], red_d[kSelWaves];
   const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
   double a = 0.0, b = 0.0;
   // unrolled so that eight loads of each array are in flight; the additions
   // keep their order
 #pragma unroll 8
-  for (int i = tid; i < L; i += kSelThreads) {
+  for (int i = tid; i < n; i += kSelThreads) {
     a += num[i];
     b += den[i];
   }
@@ -122,18 +143,34 @@ __device__ __forceinline__ void step_delta_block(const double* __restrict__ num,
 }
 
 __global__ void __launch_bounds__(kSelThreads)
-step_delta_sum(const double* __restrict__ num, const double* __restrict__ den, int L, double xi,
+step_delta_sum(const double* __restrict__ num, const double* __restrict__ den, int n, double xi,
                double* __restrict__ step_delta) {
-  step_delta_block(num, den, L, xi, step_delta);
+  step_delta_block(num, den, n, xi, step_delta);
 }
 
 // Order-preserving key: larger float -> larger key; NaN above everything; -0 == +0.
+// No float has a key below 0x007fffff (-inf), so 0 stands for "no key".
 __device__ __forceinline__ uint32_t rank_key(float s) {
-  if (s != s) return 0xffffffffu;
-  uint32_t u = __float_as_uint(s);
-  if (u == 0x80000000u) u = 0u;
-  return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+  const uint32_t u = __float_as_uint(s);
+  const uint32_t k = u ^ (static_cast<uint32_t>(static_cast<int32_t>(u) >> 31) | 0x80000000u);
+  return s != s ? 0xffffffffu : (u == 0x80000000u ? 0x80000000u : k);
 }
+
+// lanes of `mask` below this one
+__device__ __forceinline__ uint32_t lanes_below(uint64_t mask) {
+  return __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(mask >> 32),
+                                   __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(mask), 0u));
+}
+
+// LDS of one selection
+struct TopkLds {
+  uint32_t h1[2048 * 4];  // digit 1, four copies side by side (a lane uses copy lane % 4): the keys of a
+                          // step lie in a few octaves, so that most lanes of a wave meet in a few bins
+  uint32_t h2[2048], h3[1024];
+  uint32_t digit[3], above[3];
+  uint32_t tot[4][2][kSelWaves];  // wave totals of the scans (three digits, one compaction)
+  uint32_t c_gt[kSelThreads], c_eq[kSelThreads];
+};
 
 // Top-k (or threshold) selection of L keys by one 1024-thread workgroup:
 // writes mask[0..L), the selected positions i as idx_base + i in ascending
@@ -141,30 +178,87 @@ __device__ __forceinline__ uint32_t rank_key(float s) {
 // R > 0: the L keys are loaded once into registers (key r*1024 + tid in
 // slot r, L <= 1024 R), all loads in flight together; every later pass works
 // on the registers.  R == 0: keys are re-read from s on every pass (any L).
+// Workgroup `part` of `parts` writes the results of its share of the rounds
+// only: the stores of one CU take as long as the selection, and the selection,
+// repeated in every workgroup, needs no word from the others.
 template <int R>
 __device__ __forceinline__ void topk_rows(const float* __restrict__ s, int L, int k, int threshold_mode,
                                           float threshold, int idx_base, int32_t* __restrict__ idx,
-                                          uint8_t* __restrict__ mask, int32_t* __restrict__ n_sel) {
-  __shared__ uint32_t hist[256];
-  __shared__ uint32_t sh_digit, sh_above;
-  const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
-  const uint64_t lt_mask = (lane == 0) ? 0ull : ((~0ull) >> (64 - lane));
+                                          uint8_t* __restrict__ mask, int32_t* __restrict__ n_sel, int part = 0,
+                                          int parts = 1) {
+  __shared__ TopkLds lds;
+  const int tid = threadIdx.x, lane = tid % kWave;
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
 
   constexpr int RR = R > 0 ? R : 1;
   uint32_t kr[RR];
+  // The thread's index through an empty asm for each pass, and a barrier to
+  // the scheduler after each round: the indexes, addresses and bounds of up to
+  // 80 rounds, computed once and kept from pass to pass, would spill.
+  auto fresh_tid = [&]() __attribute__((always_inline)) {
+    int t = tid;
+    asm volatile("" : "+v"(t));
+    return t;
+  };
   if constexpr (R > 0) {
+    const int ta = fresh_tid();
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-      const int i = r * kSelThreads + tid;
-      kr[r] = i < L ? rank_key(s[i]) : 0u;
+      const int i = r * kSelThreads + ta;
+      kr[r] = __float_as_uint(s[i < L ? i : L - 1]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    const int tb = fresh_tid();
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      kr[r] = r * kSelThreads + tb < L ? rank_key(__uint_as_float(kr[r])) : 0u;
+      __builtin_amdgcn_sched_barrier(0);
     }
   }
   const int nr = R > 0 ? R : (L + kSelThreads - 1) / kSelThreads;
-  auto key_of = [&](int r, int i) __attribute__((always_inline)) -> uint32_t {
-    if constexpr (R > 0)
-      return kr[r];
-    else
-      return i < L ? rank_key(s[i]) : 0u;
+  // body(r, key) for the rounds r0 .. r1 - 1
+  auto for_rounds = [&](int r0, int r1, auto&& body) __attribute__((always_inline)) {
+    if constexpr (R > 0) {
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        if (r >= r0 && r < r1) body(r, kr[r]);
+        __builtin_amdgcn_sched_barrier(0);  // one round's values at a time
+      }
+    } else {
+      for (int r = r0; r < r1; ++r) {
+        const int i = r * kSelThreads + tid;
+        body(r, i < L ? rank_key(s[i]) : 0u);
+      }
+    }
+  };
+  // exclusive sums of a and b over the threads before this one, and their totals
+  auto scan2 = [&](uint32_t a, uint32_t b, uint32_t(&tot)[2][kSelWaves], uint32_t& ea, uint32_t& eb, uint32_t& ta,
+                   uint32_t& tb) __attribute__((always_inline)) {
+    uint32_t ia = a, ib = b;
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+      const uint32_t va = __shfl_up(ia, o), vb = __shfl_up(ib, o);
+      if (lane >= o) {
+        ia += va;
+        ib += vb;
+      }
+    }
+    if (lane == kWave - 1) {
+      tot[0][wave] = ia;
+      tot[1][wave] = ib;
+    }
+    __syncthreads();
+    ea = ia - a;
+    eb = ib - b;
+    ta = tb = 0;
+#pragma unroll
+    for (int w = 0; w < kSelWaves; ++w) {
+      const uint32_t va = tot[0][w], vb = tot[1][w];
+      ea += w < wave ? va : 0u;
+      eb += w < wave ? vb : 0u;
+      ta += va;
+      tb += vb;
+    }
   };
 
   // (1) threshold key and how many tokens equal to it are taken
@@ -180,174 +274,133 @@ __device__ __forceinline__ void topk_rows(const float* __restrict__ s, int L, in
     need_eq = 0;
     take_eq = true;
   } else {
-    uint32_t prefix = 0, pmask = 0, kk = static_cast<uint32_t>(k);
-    for (int pass = 0; pass < 4; ++pass) {
-      const int shift = 24 - 8 * pass;
-      for (int i = tid; i < 256; i += kSelThreads) hist[i] = 0;
-      __syncthreads();
 #pragma unroll
-      for (int r = 0; r < (R > 0 ? R : 1); ++r) {
-        for (int rr = (R > 0 ? r : 0); rr < (R > 0 ? r + 1 : nr); ++rr) {
-          const int i = rr * kSelThreads + tid;
-          const uint32_t key = key_of(rr, i);
-          const bool in = i < L && (key & pmask) == prefix;
-          const uint32_t bin = (key >> shift) & 0xffu;
-          // the lanes that share the first active lane's bin add with one atomic
-          const uint64_t act = __ballot(in);
-          if (act != 0ull) {
-            const int leader = __ffsll(static_cast<long long>(act)) - 1;
-            const uint32_t lbin = static_cast<uint32_t>(__shfl(static_cast<int>(bin), leader));
-            const uint64_t same = __ballot(in && bin == lbin);
-            if (lane == leader) atomicAdd(&hist[lbin], static_cast<uint32_t>(__popcll(same)));
-            if (in && bin != lbin) atomicAdd(&hist[bin], 1u);
-          }
-        }
+    for (int j = 0; j < 8; ++j) lds.h1[j * kSelThreads + tid] = 0;
+    lds.h2[tid] = lds.h2[kSelThreads + tid] = lds.h3[tid] = 0;
+    __syncthreads();
+    uint32_t kk = static_cast<uint32_t>(k);
+    // The bin of pass P that holds the kk-th largest key, given this thread's
+    // two counts (top bins first: thread t holds bins 2047 - 2t and 2046 - 2t),
+    // and the keys above it.
+    auto find = [&](auto p_c, uint32_t c_hi, uint32_t c_lo, uint32_t bin_hi) __attribute__((always_inline)) {
+      constexpr int P = decltype(p_c)::value;
+      uint32_t excl, dummy_e, total, dummy_t;
+      scan2(c_hi + c_lo, 0u, lds.tot[P], excl, dummy_e, total, dummy_t);
+      if (excl < kk && excl + c_hi + c_lo >= kk) {  // one thread: kk <= the keys of the digit
+        const bool hi = excl + c_hi >= kk;
+        lds.digit[P] = hi ? bin_hi : bin_hi - 1;
+        lds.above[P] = hi ? excl : excl + c_hi;
       }
       __syncthreads();
-      if (wave == 0) {
-        // lane covers bins 255-4*lane down to 252-4*lane; lane 0 holds the top bins
-        uint32_t c[4];
-        uint32_t tot = 0;
+      kk -= __builtin_amdgcn_readfirstlane(lds.above[P]);
+      return static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(lds.digit[P]));
+    };
+    // digit 1 (bits 31 .. 21); "no key" counts in bin 0, below every key's bin
+    for_rounds(0, nr, [&](int, uint32_t key) __attribute__((always_inline)) {
+      atomicAdd(&lds.h1[((key >> 21) << 2) + (lane & 3)], 1u);
+    });
+    __syncthreads();
+    uint32_t c[2];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          c[j] = hist[255 - 4 * lane - j];
-          tot += c[j];
-        }
-        uint32_t incl = tot;  // inclusive scan from lane 0
-#pragma unroll
-        for (int o = 1; o < kWave; o <<= 1) {
-          const uint32_t v = __shfl_up(incl, o);
-          if (lane >= o) incl += v;
-        }
-        const uint64_t hit = __ballot(incl >= kk);
-        const int first = __ffsll(static_cast<long long>(hit)) - 1;  // kk <= matching count
-        if (lane == first) {
-          uint32_t above = incl - tot;
-          int digit = 255 - 4 * lane;
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            if (above + c[j] >= kk) {
-              digit = 255 - 4 * lane - j;
-              break;
-            }
-            above += c[j];
-          }
-          sh_digit = static_cast<uint32_t>(digit);
-          sh_above = above;
-        }
-      }
-      __syncthreads();
-      prefix |= sh_digit << shift;
-      pmask |= 0xffu << shift;
-      kk -= sh_above;
-      __syncthreads();  // hist and sh_* are rewritten by the next pass
+    for (int j = 0; j < 2; ++j) {
+      const uint4 q = *reinterpret_cast<const uint4*>(&lds.h1[(2047 - 2 * tid - j) * 4]);
+      c[j] = q.x + q.y + q.z + q.w;
     }
-    thr = prefix;
+    uint32_t base = find(std::integral_constant<int, 0>{}, c[0], c[1], 2047u - 2u * tid) << 21;
+    // digits 2 (bits 20 .. 10) and 3 (bits 9 .. 0) of the keys in the bins before
+    for_rounds(0, nr, [&](int, uint32_t key) __attribute__((always_inline)) {
+      const uint32_t t = key - base;
+      if (t < (1u << 21)) atomicAdd(&lds.h2[t >> 10], 1u);
+    });
+    __syncthreads();
+    base += find(std::integral_constant<int, 1>{}, lds.h2[2047 - 2 * tid], lds.h2[2046 - 2 * tid], 2047u - 2u * tid) << 10;
+    for_rounds(0, nr, [&](int, uint32_t key) __attribute__((always_inline)) {
+      const uint32_t t = key - base;
+      if (t < (1u << 10)) atomicAdd(&lds.h3[t], 1u);
+    });
+    __syncthreads();
+    base += find(std::integral_constant<int, 2>{}, lds.h3[1023 - tid], 0u, 1023u - tid);
+    thr = base;
     need_eq = kk;
     take_eq = true;
   }
+
+  thr = __builtin_amdgcn_readfirstlane(thr);
+  need_eq = __builtin_amdgcn_readfirstlane(need_eq);
 
   // (2) stable compaction in index order, in chunks of CH rounds.  Round r,
   //     wave w holds the indices r * 1024 + 64 w + lane, so the (r, w) pairs
   //     taken round-major are in index order.  Per chunk:
   //   a. every wave counts its keys above (gt) and equal to (eq) the
-  //      threshold key in each round;
-  //   b. one thread per (r, w): an exclusive scan of the eq counts gives the
-  //      rank of the pair's first equal key; the equal keys taken are those
-  //      ranked below need_eq, so the pair takes gt + clamp(need_eq - rank,
-  //      0, eq) keys; an exclusive scan of those gives its first output slot;
+  //      threshold key in each round, lane r for round r;
+  //   b. one thread per (r, w): exclusive scans of both; of the equal keys
+  //      before a pair the first need_eq are taken, so its first output slot is
+  //      the keys above before it plus min(need_eq, equal keys before it);
   //   c. every lane writes its mask byte and, if taken, its index.
-  //   A handful of barriers per chunk instead of three per round.
   constexpr int CH = kSelThreads / kSelWaves;  // 64 rounds: one (r, w) pair per thread in b
-  __shared__ uint32_t c_eq[CH * kSelWaves], c_sel[CH * kSelWaves];
-  __shared__ uint32_t s_tot[kSelWaves];
-  auto for_rounds = [&](int r0, auto&& body) __attribute__((always_inline)) {
-    if constexpr (R > 0) {
-#pragma unroll
-      for (int r = 0; r < R; ++r)
-        if (r >= r0 && r < r0 + CH) body(r, kr[r]);
-    } else {
-      const int r1 = r0 + CH < nr ? r0 + CH : nr;
-      for (int r = r0; r < r1; ++r) body(r, key_of(r, r * kSelThreads + tid));
-    }
-  };
-  auto scan_excl = [&](uint32_t v, uint32_t& total) __attribute__((always_inline)) -> uint32_t {
-    uint32_t incl = v;
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-      const uint32_t t = __shfl_up(incl, o);
-      if (lane >= o) incl += t;
-    }
-    if (lane == kWave - 1) s_tot[wave] = incl;
-    __syncthreads();
-    uint32_t before = 0;
-    total = 0;
-#pragma unroll
-    for (int w = 0; w < kSelWaves; ++w) {
-      const uint32_t t = s_tot[w];
-      before += w < wave ? t : 0u;
-      total += t;
-    }
-    __syncthreads();  // s_tot is rewritten by the next scan
-    return before + incl - v;
-  };
-  uint32_t base_eq = 0, base_sel = 0;
+  uint32_t base_eq = 0, base_gt = 0;
   for (int r0 = 0; r0 < nr; r0 += CH) {
-    for_rounds(r0, [&](int r, uint32_t key) __attribute__((always_inline)) {
-      const int i = r * kSelThreads + tid;
-      const bool valid = i < L;
-      const uint64_t bgt = __ballot(valid && key > thr);
-      const uint64_t beq = __ballot(valid && take_eq && key == thr);
-      if (lane == 0) {
-        c_eq[(r - r0) * kSelWaves + wave] = static_cast<uint32_t>(__popcll(beq));
-        c_sel[(r - r0) * kSelWaves + wave] = static_cast<uint32_t>(__popcll(bgt));
-      }
+    const int r1 = r0 + CH < nr ? r0 + CH : nr;
+    uint32_t n_gt = 0, n_eq = 0;
+    for_rounds(r0, r1, [&](int r, uint32_t key) __attribute__((always_inline)) {
+      const uint64_t bgt = __ballot(key > thr), beq = __ballot(take_eq && key == thr);
+      const bool mine = lane == r - r0;
+      n_gt = mine ? static_cast<uint32_t>(__popcll(bgt)) : n_gt;
+      n_eq = mine ? static_cast<uint32_t>(__popcll(beq)) : n_eq;
     });
+    lds.c_gt[lane * kSelWaves + wave] = n_gt;  // 0 past the last round
+    lds.c_eq[lane * kSelWaves + wave] = n_eq;
     __syncthreads();
-    const bool ent = r0 + tid / kSelWaves < nr;  // this thread's pair exists
-    const uint32_t veq = ent ? c_eq[tid] : 0u, vgt = ent ? c_sel[tid] : 0u;
-    uint32_t tot_eq, tot_sel;
-    const uint32_t rank = base_eq + scan_excl(veq, tot_eq);
-    const uint32_t take = need_eq > rank ? (need_eq - rank < veq ? need_eq - rank : veq) : 0u;
-    const uint32_t first = base_sel + scan_excl(vgt + take, tot_sel);
-    c_eq[tid] = rank;
-    c_sel[tid] = first;
+    uint32_t gt, eq, tot_gt, tot_eq;
+    scan2(lds.c_gt[tid], lds.c_eq[tid], lds.tot[3], gt, eq, tot_gt, tot_eq);
+    const uint32_t rank = base_eq + eq;  // of the pair's first equal key
+    lds.c_eq[tid] = rank;
+    lds.c_gt[tid] = base_gt + gt + (rank < need_eq ? rank : need_eq);
+    base_gt += tot_gt;
     base_eq += tot_eq;
-    base_sel += tot_sel;
     __syncthreads();
-    for_rounds(r0, [&](int r, uint32_t key) __attribute__((always_inline)) {
-      const int i = r * kSelThreads + tid;
-      const bool valid = i < L;
-      const bool gt = valid && key > thr;
-      const bool eq = valid && take_eq && key == thr;
-      const uint64_t beq = __ballot(eq);
-      const uint32_t eq_before = c_eq[(r - r0) * kSelWaves + wave] + static_cast<uint32_t>(__popcll(beq & lt_mask));
-      const bool sel = gt || (eq && eq_before < need_eq);
-      const uint64_t bsel = __ballot(sel);
-      const uint32_t pos = c_sel[(r - r0) * kSelWaves + wave] + static_cast<uint32_t>(__popcll(bsel & lt_mask));
-      if (valid) {
+    // (the comparisons of a. done again, not their 64-bit results kept: two per
+    // round would spill)
+    asm volatile("" : "+s"(thr));
+    const int w0 = static_cast<int>(static_cast<int64_t>(nr) * part / parts);
+    const int w1 = static_cast<int>(static_cast<int64_t>(nr) * (part + 1) / parts);
+    const int tc = fresh_tid();
+    const uint32_t my_rank = lds.c_eq[lane * kSelWaves + wave], my_first = lds.c_gt[lane * kSelWaves + wave];
+    for_rounds(r0 > w0 ? r0 : w0, r1 < w1 ? r1 : w1, [&](int r, uint32_t key) __attribute__((always_inline)) {
+      const int i = r * kSelThreads + tc;
+      bool sel = key > thr;
+      uint64_t bsel = __ballot(sel);
+      const uint64_t beq = __ballot(take_eq && key == thr);
+      if (beq != 0ull) {  // uniform
+        const uint32_t before = __builtin_amdgcn_readlane(my_rank, r - r0) + lanes_below(beq);
+        sel = sel || (take_eq && key == thr && before < need_eq);
+        bsel = __ballot(sel);
+      }
+      const uint32_t pos = __builtin_amdgcn_readlane(my_first, r - r0) + lanes_below(bsel);
+      if (i < L) {
         mask[i] = sel ? 1 : 0;
         if (sel) idx[pos] = idx_base + i;
       }
     });
-    __syncthreads();  // c_eq / c_sel are rewritten by the next chunk
+    __syncthreads();  // c_gt / c_eq and the scan totals are rewritten by the next chunk
   }
-  if (tid == 0 && n_sel != nullptr) *n_sel = static_cast<int32_t>(base_sel);
+  if (tid == 0 && part == 0 && n_sel != nullptr)
+    *n_sel = static_cast<int32_t>(base_gt + (base_eq < need_eq ? base_eq : need_eq));
 }
 
-// Workgroup 0 selects; workgroup 1 (launched only when step_delta is not
+// Workgroups [0, parts) select; one more (launched only when step_delta is not
 // null) computes the step-level sum, independently of the selection.
 template <int R>
 __global__ void __launch_bounds__(kSelThreads)
 select_rows(const float* __restrict__ s, int L, int k, int threshold_mode, float threshold,
             int32_t* __restrict__ idx, uint8_t* __restrict__ mask, int32_t* __restrict__ n_sel,
-            const double* __restrict__ num, const double* __restrict__ den, double xi,
-            double* __restrict__ step_delta) {
-  if (blockIdx.x == 1) {
-    step_delta_block(num, den, L, xi, step_delta);
+            const double* __restrict__ num, const double* __restrict__ den, int nsums, double xi,
+            double* __restrict__ step_delta, int parts) {
+  if (static_cast<int>(blockIdx.x) == parts) {
+    step_delta_block(num, den, nsums, xi, step_delta);
     return;
   }
-  topk_rows<R>(s, L, k, threshold_mode, threshold, 0, idx, mask, n_sel);
+  topk_rows<R>(s, L, k, threshold_mode, threshold, 0, idx, mask, n_sel, blockIdx.x, parts);
 }
 
 // Two-stage selection: workgroup t handles segment t (tokens [tN, tN + N)).
@@ -423,10 +476,13 @@ anchor_select(const float* __restrict__ keys, int T, int k, int mode, uint8_t* _
   }
 }
 
+// workgroups of the saliency pass, each of which leaves one pair of sums
+static int sal_parts(int L) { return (L + (kSalThreads / kWave) - 1) / (kSalThreads / kWave); }
+
 hipError_t launch_saliency(int dtype_bf16, const void* x, const void* xref, const float* fw, int L, int N,
                            int D, double xi, float* s, double* num, double* den, double* step_delta,
                            hipStream_t stream) {
-  const dim3 grid((L + (kSalThreads / kWave) - 1) / (kSalThreads / kWave));
+  const dim3 grid(sal_parts(L));
   const int per_lane = (D / 8 + kWave - 1) / kWave;
   hipError_t e = hipErrorInvalidValue;
   bool done = false;
@@ -454,24 +510,28 @@ hipError_t launch_saliency(int dtype_bf16, const void* x, const void* xref, cons
   ECHO_SAL_CASE(0)
 #undef ECHO_SAL_CASE
   if (e != hipSuccess || step_delta == nullptr) return e;
-  return ECHO_LAUNCH("step_delta_sum", step_delta_sum, dim3(1), dim3(kSelThreads), 0, stream, num, den, L,
-                     xi, step_delta);
+  return ECHO_LAUNCH("step_delta_sum", step_delta_sum, dim3(1), dim3(kSelThreads), 0, stream, num, den,
+                     sal_parts(L), xi, step_delta);
 }
 
 hipError_t launch_topk(const float* s, int L, int k, int threshold_mode, float threshold, int32_t* idx,
                        uint8_t* mask, int32_t* n_sel, hipStream_t stream, const double* num,
                        const double* den, double xi, double* step_delta) {
-  const dim3 grid(step_delta != nullptr ? 2 : 1);
+  // four rounds of stores per workgroup, up to one workgroup per XCD
+  const int rounds = (L + kSelThreads - 1) / kSelThreads;
+  const int parts = rounds < 8 ? 1 : rounds / 4 < 8 ? rounds / 4 : 8;
+  const dim3 grid(parts + (step_delta != nullptr ? 1 : 0));
 #define ECHO_SEL_CASE(RK)                                                                      \
   if (L <= RK * kSelThreads)                                                                   \
     return ECHO_LAUNCH("select_rows", select_rows<RK>, grid, dim3(kSelThreads), 0, stream, s, L, \
-                       k, threshold_mode, threshold, idx, mask, n_sel, num, den, xi, step_delta);
+                       k, threshold_mode, threshold, idx, mask, n_sel, num, den, sal_parts(L), xi, step_delta, parts);
+  ECHO_SEL_CASE(1)
   ECHO_SEL_CASE(8)
   ECHO_SEL_CASE(32)
   ECHO_SEL_CASE(80)
 #undef ECHO_SEL_CASE
   return ECHO_LAUNCH("select_rows", select_rows<0>, grid, dim3(kSelThreads), 0, stream, s, L, k,
-                     threshold_mode, threshold, idx, mask, n_sel, num, den, xi, step_delta);
+                     threshold_mode, threshold, idx, mask, n_sel, num, den, sal_parts(L), xi, step_delta, parts);
 }
 
 hipError_t launch_topk_segments(const float* s, const uint8_t* anchors, int T, int N, int k, int32_t* idx,
