@@ -23,7 +23,7 @@
 // passes are kept to a few (a shift and an LDS add in the first, a subtract and a
 // compare for the keys outside the digit in the others; a wave's counts in its lanes).
 // Four passes of 8 bits with a leader election per 64 keys and a count written
-// per (round, wave) took 36.5 us at 32760 keys, this form 24.7; 75600 keys 150 -> 67.
+// per (round, wave) took 36.5 us at 32760 keys, this form 24.7; at 75600 keys 147 and 62.6.
 // select_segments: the same selection per anchor segment, one workgroup per
 //   segment (the two-stage form: anchor segments, then min(k, N) tokens each).
 // anchor_select: the anchor segments (top-k of per-segment keys, or evenly

@@ -40,6 +40,48 @@ def test_saliency_then_topk_is_select(w):
         assert np.array_equal(got.view(np.uint8), v.view(np.uint8)), n
 
 
+def _hard_saliency(L, kind, seed):
+    """Keys that meet the edges of a digit-wise selection: specials and signed
+    zeros, one value everywhere, and values that differ in the lowest bits only."""
+    rng = np.random.default_rng(seed)
+    if kind == "special":
+        pool = np.array([np.nan, np.inf, -np.inf, 0.0, -0.0, 1e-45, -1e-45, 1.0, -1.0, 3.4028235e38], np.float32)
+        s = np.where(rng.random(L) < 0.5, pool[rng.integers(0, pool.size, L)], rng.standard_normal(L))
+        return s.astype(np.float32)
+    if kind == "equal":
+        return np.full(L, 0.25, np.float32)
+    bits = np.float32(0.75).view(np.uint32) + rng.integers(0, 4096, L).astype(np.uint32)
+    return bits.astype(np.uint32).view(np.float32)
+
+
+@pytest.mark.parametrize("kind", ["special", "equal", "low_bits"])
+@pytest.mark.parametrize("L", [1, 1023, 1025, 7168, 8193, 32768, 32769, 81920, 81921])
+def test_topk_edges(L, kind):
+    """Sizes at the edges of the register forms and of the shared stores (from
+    8 rounds of 1024 keys), against a sort by (NaN first, value, index); exact."""
+    s = _hard_saliency(L, kind, L)
+    order = np.lexsort((np.arange(L), -np.where(np.isnan(s), 0.0, s.astype(np.float64)), ~np.isnan(s)))
+    S = up(s)
+    cases = [("k", k, np.sort(order[:k])) for k in sorted({0, 1, L // 3, L - 1, L})]
+    thr = float(s[~np.isnan(s)].max()) if kind == "equal" else 0.75
+    cases += [("threshold", t, np.flatnonzero(np.isnan(s) | (s > np.float32(t)))) for t in (thr, -1.0)]
+    for mode, v, want in cases:
+        say(f"topk L={L} {kind} {mode}={v}")
+        sel = api.Selection(idx=torch.full((L,), -1, dtype=torch.int32, device=device()),
+                            mask=torch.full((L,), 7, dtype=torch.uint8, device=device()),
+                            n_sel_dev=torch.empty(1, dtype=torch.int32, device=device()), n_sel=None,
+                            saliency=S, step_delta=None)
+        api.topk(sel, L, 64, torch.float32, **{mode: v})
+        torch.cuda.synchronize()
+        idx, mask = down(sel.idx), down(sel.mask)
+        m = np.zeros(L, np.uint8)
+        m[want] = 1
+        assert int(sel.n_sel_dev.item()) == want.size, (mode, v)
+        assert np.array_equal(idx[:want.size], want), (mode, v)
+        assert (idx[want.size:] == -1).all(), (mode, v)      # nothing past the selected ones is written
+        assert np.array_equal(mask, m), (mode, v)
+
+
 def _trajectory(w, steps, seed=7):
     rng = np.random.default_rng(seed)
     from oracle.cache import cast_act
