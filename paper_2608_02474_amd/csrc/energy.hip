@@ -2,9 +2,8 @@
 // STFT power, pooled into mel-width bands and latent frames.
 //
 // Kernel 1 (energy_frames): one workgroup per (segment, STFT frame), in fp64.
-// For a power-of-two n_fft, an in-place radix-2 FFT in LDS (log2 n_fft
-// barrier-separated butterfly stages); for any other even n_fft, each thread
-// evaluates whole one-sided bins k directly from the DFT sum over a
+// For a power-of-two n_fft, an in-place FFT in LDS; for any other even n_fft,
+// each thread evaluates whole one-sided bins k directly from the DFT sum over a
 // full-period twiddle table.  |X_k|^2 and each bin's band go to LDS, and one
 // wave per band sums its bins.  Both stay within fp64 rounding of the
 // definition.
@@ -17,10 +16,10 @@
 
 namespace echo {
 
-constexpr int kEnergyThreads = 256;   // energy_reduce (power of two: tree reduction)
+constexpr int kEnergyThreads = 256;   // energy_reduce
+constexpr int kLdsSums = 2048;        // band sums that energy_reduce holds in LDS
 constexpr int kFrameThreads = 512;    // energy_frames: one thread per one-sided bin up to n_fft 1022
 constexpr int kFftThreads = 256;     // energy_frames_fft
-constexpr int kMaxFft = 2048;
 
 __device__ __forceinline__ int band_of_bin(int k, int n_fft, int sr, int n_bands) {
   const double mel_top = 2595.0 * log10(1.0 + (0.5 * sr) / 700.0);
@@ -45,21 +44,34 @@ __device__ __forceinline__ void band_sums(const double* pw, const int* bandof, i
   }
 }
 
-// Radix-2 path for a power-of-two n_fft: one workgroup of kFftThreads per
-// (segment, frame).  The windowed frame is placed in bit-reversed order and
-// transformed in place by log2(n_fft) decimation-in-time butterfly stages in
-// fp64 (twiddles exp(-2 pi i j / n_fft) from an LDS table); then the one-sided
-// powers and the band sums as in the direct path.
+__device__ __forceinline__ double2 cadd(double2 a, double2 b) { return make_double2(a.x + b.x, a.y + b.y); }
+__device__ __forceinline__ double2 csub(double2 a, double2 b) { return make_double2(a.x - b.x, a.y - b.y); }
+__device__ __forceinline__ double2 cmul(double2 a, double2 w) {
+  return make_double2(a.x * w.x - a.y * w.y, a.x * w.y + a.y * w.x);
+}
+
+// Power-of-two n_fft (16 .. 2048): one workgroup of kFftThreads per (segment,
+// frame), decimation in frequency in fp64: natural order in, X_k at position
+// bitrev(k).  The chain of dependent steps bounds it (a frame is 2 KB), so
+// there are few of them: a thread makes the window and the twiddle of j from
+// one sincospi and does the first stage on samples j and j + n_fft/2 as it
+// loads them; the band of bin j is worked out while the samples are on their
+// way; the other stages go two at a time, and the last two leave the powers of
+// the one-sided bins (the even positions and position 1).  Bands are ranges of
+// bins, so that a wave sums its band's range and no other.  441 frames of 512:
+// 7.2 us; one stage per barrier from a bit-reversed load, a second cosine for
+// the window and masked band sums over all bins took 10.4.
 __global__ void __launch_bounds__(kFftThreads)
 energy_frames_fft(const float* __restrict__ audio, int64_t n_samples, int T, int n_fft, int log2n, int hop,
                   int n_bands, int sr, int max_frames, double* __restrict__ part) {
-  extern __shared__ double lds[];
-  double* re = lds;                       // [n_fft]
-  double* im = lds + n_fft;               // [n_fft]
-  double* twc = lds + 2 * n_fft;          // [n_fft/2] cos(2 pi j / n_fft)
-  double* tws = twc + n_fft / 2;          // [n_fft/2] -sin(2 pi j / n_fft)
-  double* pw = tws + n_fft / 2;           // [n_fft/2 + 1]
-  int* bandof = reinterpret_cast<int*>(pw + n_fft / 2 + 1);  // [n_fft/2 + 1]
+  extern __shared__ __attribute__((aligned(16))) double lds[];
+  const int half = n_fft / 2;
+  double2* z = reinterpret_cast<double2*>(lds);               // [n_fft]
+  double2* tw = z + n_fft;                                    // [n_fft/2] exp(-2 pi i j / n_fft)
+  double* pw = reinterpret_cast<double*>(tw + half);          // [n_fft/2 + 1]
+  int* bandof = reinterpret_cast<int*>(pw + half + 1);        // [n_fft/2 + 1]
+  int* first = bandof + half + 1;                             // [n_bands + 1] first bin of a band
+  const int tid = threadIdx.x;
   const int t = blockIdx.y, f = blockIdx.x;
   const int64_t a = (static_cast<int64_t>(t) * n_samples) / T;
   const int64_t b = (static_cast<int64_t>(t + 1) * n_samples) / T;
@@ -67,49 +79,80 @@ energy_frames_fft(const float* __restrict__ audio, int64_t n_samples, int T, int
   const int nf = len < n_fft ? 1 : static_cast<int>(1 + (len - n_fft) / hop);
   double* out = part + (static_cast<int64_t>(t) * max_frames + f) * n_bands;
   if (f >= nf) {
-    for (int i = threadIdx.x; i < n_bands; i += blockDim.x) out[i] = 0.0;
+    for (int i = tid; i < n_bands; i += kFftThreads) out[i] = 0.0;
     return;
   }
   const int64_t start = a + static_cast<int64_t>(f) * hop;
-  for (int n = threadIdx.x; n < n_fft; n += blockDim.x) {
-    const double w = 0.5 - 0.5 * cospi(2.0 * n / n_fft);  // periodic Hann
-    const int64_t sidx = start + n;
-    const double v = (sidx < b) ? static_cast<double>(audio[sidx]) : 0.0;
-    const int r = static_cast<int>(__brev(static_cast<unsigned>(n)) >> (32 - log2n));
-    re[r] = w * v;
-    im[r] = 0.0;
-  }
-  for (int j = threadIdx.x; j < n_fft / 2; j += blockDim.x) {
+  const int64_t last = b - 1;
+  for (int j = tid; j < half; j += kFftThreads) {
+    const int64_t i0 = start + j, i1 = i0 + half;
+    const float s0 = audio[i0 < b ? i0 : last], s1 = audio[i1 < b ? i1 : last];
     double sn, cs;
     sincospi(2.0 * j / n_fft, &sn, &cs);
-    twc[j] = cs;
-    tws[j] = -sn;
+    bandof[j] = band_of_bin(j, n_fft, sr, n_bands);
+    const double2 w = make_double2(cs, -sn);
+    // periodic Hann 0.5 - 0.5 cos(2 pi n / n_fft); the cosine half a period on is -cs
+    const double v0 = i0 < b ? (0.5 - 0.5 * cs) * static_cast<double>(s0) : 0.0;
+    const double v1 = i1 < b ? (0.5 + 0.5 * cs) * static_cast<double>(s1) : 0.0;
+    const double d = v0 - v1;
+    tw[j] = w;
+    z[j] = make_double2(v0 + v1, 0.0);
+    z[j + half] = make_double2(d * w.x, d * w.y);
+  }
+  if (tid == 0) {
+    bandof[half] = n_bands - 1;  // half the sampling rate: the top of the last band
+    first[n_bands] = half + 1;
   }
   __syncthreads();
-  for (int st = 1; st <= log2n; ++st) {
-    const int half = 1 << (st - 1);
-    for (int bf = threadIdx.x; bf < n_fft / 2; bf += blockDim.x) {
-      const int pos = bf & (half - 1);
-      const int i0 = ((bf >> (st - 1)) << st) + pos, i1 = i0 + half;
-      const int tw = pos << (log2n - st);
-      const double wr = twc[tw], wi = tws[tw];
-      const double br = re[i1], bi = im[i1];
-      const double xr = br * wr - bi * wi, xi = br * wi + bi * wr;
-      const double ar = re[i0], ai = im[i0];
-      re[i0] = ar + xr;
-      im[i0] = ai + xi;
-      re[i1] = ar - xr;
-      im[i1] = ai - xi;
+  for (int k = tid; k <= half; k += kFftThreads)
+    for (int band = k > 0 ? bandof[k - 1] + 1 : 0; band <= bandof[k]; ++band) first[band] = k;
+  int left = log2n - 1;  // stages still to do, each on blocks of 2^left
+  if (left & 1) {
+    const int h = 1 << (left - 1);
+    for (int i = tid; i < half; i += kFftThreads) {
+      const int pos = i & (h - 1), p0 = 2 * i - pos;
+      const double2 x0 = z[p0], x1 = z[p0 + h], w = tw[pos << (log2n - left)];
+      z[p0] = cadd(x0, x1);
+      z[p0 + h] = cmul(csub(x0, x1), w);
+    }
+    __syncthreads();
+    --left;
+  }
+  for (; left > 0; left -= 2) {
+    const int lq = left - 2, q = 1 << lq;
+    for (int i = tid; i < n_fft / 4; i += kFftThreads) {
+      const int pos = i & (q - 1), p0 = 4 * i - 3 * pos;
+      const double2 x0 = z[p0], x1 = z[p0 + q], x2 = z[p0 + 2 * q], x3 = z[p0 + 3 * q];
+      const double2 w1 = tw[pos << (log2n - left)], w2 = tw[pos << (log2n - left + 1)];
+      const double2 u0 = cadd(x0, x2), u1 = cadd(x1, x3);
+      const double2 u2 = cmul(csub(x0, x2), w1);
+      const double2 e = cmul(csub(x1, x3), w1), u3 = make_double2(e.y, -e.x);  // times -i
+      if (left > 2) {
+        z[p0] = cadd(u0, u1);
+        z[p0 + q] = cmul(csub(u0, u1), w2);
+        z[p0 + 2 * q] = cadd(u2, u3);
+        z[p0 + 3 * q] = cmul(csub(u2, u3), w2);
+      } else {  // q == 1, w1 == w2 == 1
+        const double2 y0 = cadd(u0, u1), y2 = cadd(u2, u3);
+        const int k = static_cast<int>(__brev(static_cast<unsigned>(4 * i)) >> (32 - log2n));
+        pw[k] = y0.x * y0.x + y0.y * y0.y;
+        pw[k + n_fft / 4] = y2.x * y2.x + y2.y * y2.y;  // bit 1 of the position is bit log2n - 2 of the bin
+        if (i == 0) {
+          const double2 y1 = csub(u0, u1);
+          pw[half] = y1.x * y1.x + y1.y * y1.y;
+        }
+      }
     }
     __syncthreads();
   }
-  const int nbins = n_fft / 2 + 1;
-  for (int k = threadIdx.x; k < nbins; k += blockDim.x) {
-    pw[k] = re[k] * re[k] + im[k] * im[k];
-    bandof[k] = band_of_bin(k, n_fft, sr, n_bands);
+  const int wave = tid / kWave, lane = tid % kWave;
+  for (int band = wave; band < n_bands; band += kFftThreads / kWave) {
+    double acc = 0.0;
+    const int k1 = first[band + 1];
+    for (int k = first[band] + lane; k < k1; k += kWave) acc += pw[k];
+    acc = wave_sum(acc);
+    if (lane == 0) out[band] = acc;
   }
-  __syncthreads();
-  band_sums(pw, bandof, nbins, n_bands, out);
 }
 
 __global__ void __launch_bounds__(kFrameThreads)
@@ -178,45 +221,64 @@ energy_frames(const float* __restrict__ audio, int64_t n_samples, int T, int n_f
   band_sums(pw, bandof, nbins, n_bands, out);
 }
 
+// One workgroup: three dependent steps, so that the memory in flight and the
+// words between the steps are what it takes; the band sums and the energies
+// stay in LDS and registers where they fit (T n_bands <= kLdsSums, T <= the
+// threads), in e_scratch otherwise.  21 segments, 8 bands, 21 frames: 2.8 us;
+// with 8 loads in flight, band sums through global memory and a tree of
+// barriers for the maximum 5.2.
 __global__ void __launch_bounds__(kEnergyThreads)
 energy_reduce(const double* __restrict__ part, int T, int max_frames, int n_bands,
               float* __restrict__ band_energy, float* __restrict__ frame_energy,
               float* __restrict__ frame_weight, double* __restrict__ e_scratch) {
-  __shared__ double red[kEnergyThreads];
+  __shared__ double sums[kLdsSums];
+  __shared__ double red[kEnergyThreads / kWave];
+  const int tid = threadIdx.x;
   // (1) one thread per (segment, band): the band's frames summed in frame
-  //     order; the fp64 band sums go to e_scratch[T + t * n_bands + band]
+  //     order, the loads of kInFlight frames together
   double* bsum = e_scratch + T;
-  for (int i = threadIdx.x; i < T * n_bands; i += blockDim.x) {
+  const bool in_lds = T * n_bands <= kLdsSums;
+  constexpr int kInFlight = 24;
+  for (int i = tid; i < T * n_bands; i += kEnergyThreads) {
     const int t = i / n_bands, band = i % n_bands;
     const double* src = part + static_cast<int64_t>(t) * max_frames * n_bands + band;
     double acc = 0.0;
-    // unrolled so that eight frames' loads are in flight; the additions keep
-    // frame order
-#pragma unroll 8
-    for (int f = 0; f < max_frames; ++f) acc += src[static_cast<int64_t>(f) * n_bands];
-    bsum[i] = acc;
+    for (int f0 = 0; f0 < max_frames; f0 += kInFlight) {
+      double v[kInFlight];
+#pragma unroll
+      for (int u = 0; u < kInFlight; ++u)
+        v[u] = src[static_cast<int64_t>(f0 + u < max_frames ? f0 + u : max_frames - 1) * n_bands];
+#pragma unroll
+      for (int u = 0; u < kInFlight; ++u) acc += f0 + u < max_frames ? v[u] : 0.0;
+    }
+    if (in_lds) sums[i] = acc;
+    else bsum[i] = acc;
     band_energy[i] = static_cast<float>(acc);
   }
   __syncthreads();
   // (2) one thread per segment: its bands in band order
-  double local_max = 0.0;
-  for (int t = threadIdx.x; t < T; t += blockDim.x) {
+  double local_max = 0.0, e_mine = 0.0;
+  for (int t = tid; t < T; t += kEnergyThreads) {
     double tot = 0.0;
-    for (int band = 0; band < n_bands; ++band) tot += bsum[t * n_bands + band];
+    if (in_lds)
+      for (int band = 0; band < n_bands; ++band) tot += sums[t * n_bands + band];
+    else
+      for (int band = 0; band < n_bands; ++band) tot += bsum[t * n_bands + band];
     const double e = sqrt(tot);
-    e_scratch[t] = e;
+    if (t == tid) e_mine = e;
+    else e_scratch[t] = e;
     frame_energy[t] = static_cast<float>(e);
     local_max = fmax(local_max, e);
   }
-  red[threadIdx.x] = local_max;
+#pragma unroll
+  for (int o = kWave / 2; o > 0; o >>= 1) local_max = fmax(local_max, __shfl_xor(local_max, o));
+  if (tid % kWave == 0) red[tid / kWave] = local_max;
   __syncthreads();
-  for (int s = blockDim.x / 2; s > 0; s >>= 1) {
-    if (threadIdx.x < s) red[threadIdx.x] = fmax(red[threadIdx.x], red[threadIdx.x + s]);
-    __syncthreads();
-  }
-  const double mx = red[0];
-  for (int t = threadIdx.x; t < T; t += blockDim.x)
-    frame_weight[t] = mx > 0.0 ? static_cast<float>(e_scratch[t] / mx) : 1.0f;
+  double mx = red[0];
+#pragma unroll
+  for (int w = 1; w < kEnergyThreads / kWave; ++w) mx = fmax(mx, red[w]);
+  for (int t = tid; t < T; t += kEnergyThreads)
+    frame_weight[t] = mx > 0.0 ? static_cast<float>((t == tid ? e_mine : e_scratch[t]) / mx) : 1.0f;
 }
 
 int energy_max_frames(int64_t n_samples, int T, int n_fft, int hop) {
@@ -233,7 +295,7 @@ hipError_t launch_energy(const float* audio, int64_t n_samples, int T, int sr, i
   if ((n_fft & (n_fft - 1)) == 0) {
     int log2n = 0;
     while ((1 << log2n) < n_fft) ++log2n;
-    const size_t lds = sizeof(double) * (3 * n_fft + n_fft / 2 + 1) + sizeof(int) * (n_fft / 2 + 1);
+    const size_t lds = sizeof(double) * (3 * n_fft + n_fft / 2 + 1) + sizeof(int) * (n_fft / 2 + 2 + n_bands);
     e = ECHO_LAUNCH("energy_frames", energy_frames_fft, dim3(mf, T), dim3(kFftThreads), lds, stream, audio,
                     n_samples, T, n_fft, log2n, hop, n_bands, sr, mf, part);
   } else {

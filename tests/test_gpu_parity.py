@@ -63,6 +63,24 @@ def test_energy_other_stft_sizes(n_fft, hop, bands):
         assert (err <= 1e-6 * np.abs(want.astype(np.float64))).all(), (name, float(err.max()))
 
 
+@pytest.mark.parametrize("n_fft,hop,bands,T,n", [(16, 5, 64, 3, 900), (32, 16, 5, 2, 700), (64, 9, 1, 1, 3000),
+                                                 (1024, 300, 9, 4, 30000), (16, 16, 16, 300, 9000),
+                                                 (2048, 1500, 64, 33, 69300), (512, 512, 8, 7, 7)])
+def test_energy_fft_stages_and_sums(n_fft, hop, bands, T, n):
+    """Odd and even numbers of stages, empty bands, more frames than the sum
+    keeps in flight, and more band sums and segments than it holds on chip.
+    The sums are in 64 bits, so that the fp32 results differ by rounding
+    (6e-8) only."""
+    say(f"energy n_fft={n_fft} hop={hop} bands={bands} T={T} n={n}")
+    audio = synth.make_audio("noise", n, 16000, seed=13)
+    Eb, e, w = OE.energy(audio, T, 16000, n_fft, hop, bands)
+    gb, ge, gw = api.energy(up(audio), T, 16000, n_fft, hop, bands)
+    torch.cuda.synchronize()
+    for got, want, name in ((down(gb), Eb, "band"), (down(ge), e, "frame"), (down(gw), w, "weight")):
+        err = np.abs(got.astype(np.float64) - want)
+        assert (err <= 2e-7 * np.abs(want.astype(np.float64)) + 1e-30).all(), (name, float(err.max()))
+
+
 # ------------------------------------------------------------------- select
 
 def _frame_weight(w, profile=None):
