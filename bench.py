@@ -625,8 +625,8 @@ def wan_leg(w, dev, dt, B: int = 2, Lc: int = 512, steps: int = 10):
         kernels[name] = e
     tf = roofline.wan_block_flops(B, L, K, D, F, Lc) / (ms * 1e-3) / 1e12
     extra = sum(kernels[n]["ms_per_call"] for n in kernels
-                if n.startswith(("qk_norm_rope", "gemm_qkvc", "gemm_qc", "gemm_kvc", "gemm_oc", "attn_cross", "rope_table",
-                                 "vec_shift")))
+                if n.startswith(("qk_norm_rope", "gemm_qkvc", "gemm_qc", "gemm_kvc", "gemm_oc", "attn_cross",
+                                 "wan_constants")))
     return {"batch": B, "context_tokens": Lc, "selected_per_element": K, "ms_per_call": round(ms, 3),
             "tokens_per_s": round(B * L / (ms * 1e-3), 1), "tflops": round(tf, 1),
             "frac_bf16_peak": round(tf / roofline.PEAK_BF16_TFLOPS, 4),

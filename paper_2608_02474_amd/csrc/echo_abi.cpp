@@ -601,9 +601,7 @@ int echo_wan_block_partial(const echo_wan_block_cfg* cfg, const echo_wan_block_w
 #define ECHO_TRY(call)                              \
   if ((e = (call)) != hipSuccess) return device_status(e);
   // constants: rotary table, the unit gate of the cross-attention output, g3 - 1
-  ECHO_TRY(launch_rope_table(cfg->T, cfg->gh, cfg->gw, dh, cfg->rope_base, ws.tab, st));
-  ECHO_TRY(launch_vec_shift(nullptr, 1.0f, ws.ones, D, st));
-  ECHO_TRY(launch_vec_shift(w->g3, -1.0f, ws.g3m1, D, st));
+  ECHO_TRY(launch_wan_constants(cfg->T, cfg->gh, cfg->gw, dh, cfg->rope_base, ws.tab, w->g3, ws.ones, ws.g3m1, D, st));
   // self-attention
   ECHO_TRY(launch_modln_input(1, x, BL, D, mod + 0 * D, mod + 1 * D, cfg->ln_eps, ws.a, st));
   const GemmBf16Args gq{static_cast<P>(ws.a), D, idx, BL, static_cast<P>(w->self.wq), static_cast<P>(w->self.wq), D, D,
@@ -613,10 +611,9 @@ int echo_wan_block_partial(const echo_wan_block_cfg* cfg, const echo_wan_block_w
                    D, static_cast<P>(w->self.bk), static_cast<P>(w->self.bv), BL, 2 * D, D, ws.kv, 2 * D,
                    nullptr, nullptr, 0, nullptr, 0};
   ECHO_TRY(launch_gemm_bf16_pair("gemm_qkv_bf16", "gemm_q_bf16", "gemm_kv_bf16", with_part(gq), with_part(g), st));
-  ECHO_TRY(launch_qk_norm_rope(static_cast<bf16_t*>(ws.q), D, n, D, w->gq, cfg->rms_eps, idx, ws.tab, L, cfg->T,
-                               cfg->gh, cfg->gw, dh, st));
-  ECHO_TRY(launch_qk_norm_rope(static_cast<bf16_t*>(ws.kv), 2 * D, BL, D, w->gk, cfg->rms_eps, nullptr, ws.tab, L,
-                               cfg->T, cfg->gh, cfg->gw, dh, st));
+  ECHO_TRY(launch_qk_norm_rope(QkRows{static_cast<bf16_t*>(ws.q), D, n, w->gq, idx},
+                               QkRows{static_cast<bf16_t*>(ws.kv), 2 * D, BL, w->gk, nullptr}, D, cfg->rms_eps,
+                               ws.tab, L, cfg->T, cfg->gh, cfg->gw, dh, st));
   {
     const bf16_t* kvp = static_cast<const bf16_t*>(ws.kv);
     int64_t o = 0;
@@ -640,10 +637,9 @@ int echo_wan_block_partial(const echo_wan_block_cfg* cfg, const echo_wan_block_w
                    static_cast<P>(w->bkc), static_cast<P>(w->bvc), BLc, 2 * D, D, ws.kvc, 2 * D,
                    nullptr, nullptr, 0, nullptr, 0};
   ECHO_TRY(launch_gemm_bf16_pair("gemm_qkvc_bf16", "gemm_qc_bf16", "gemm_kvc_bf16", with_part(gqc), with_part(g), st));
-  ECHO_TRY(launch_qk_norm_rope(static_cast<bf16_t*>(ws.q), D, n, D, w->gqc, cfg->rms_eps, nullptr, nullptr, L,
-                               cfg->T, cfg->gh, cfg->gw, dh, st));
-  ECHO_TRY(launch_qk_norm_rope(static_cast<bf16_t*>(ws.kvc), 2 * D, BLc, D, w->gkc, cfg->rms_eps, nullptr, nullptr,
-                               L, cfg->T, cfg->gh, cfg->gw, dh, st));
+  ECHO_TRY(launch_qk_norm_rope(QkRows{static_cast<bf16_t*>(ws.q), D, n, w->gqc, nullptr},
+                               QkRows{static_cast<bf16_t*>(ws.kvc), 2 * D, BLc, w->gkc, nullptr}, D, cfg->rms_eps,
+                               nullptr, L, cfg->T, cfg->gh, cfg->gw, dh, st));
   {
     const bf16_t* kvp = static_cast<const bf16_t*>(ws.kvc);
     int64_t o = 0;

@@ -105,15 +105,21 @@ hipError_t launch_refcache_update(int dtype_bf16, const void* x, const int32_t* 
                                   int32_t* chain_ref, int32_t* ent_slot, uint8_t* ent_kind, int8_t* codes,
                                   float* scale, void* xref, void* y, hipStream_t stream);
 
-// Wan-style block extras: rotary table ((cos, sin) per axis position and pair),
-// in-place qk RMSNorm (+ 3D RoPE when tab is not null) of M rows of z, and
-// out = (a ? a : 0) + beta
+// Wan-style block extras: the rotary table ((cos, sin) per axis position and
+// pair) with ones = 1 and g3m1 = g3 - 1, and the in-place qk RMSNorm (+ 3D RoPE
+// when tab is not null) of the rows of a and of b
+struct QkRows {
+  bf16_t* z;
+  int64_t ldz;
+  int M;
+  const float* g;
+  const int32_t* rows;  // token of row m; null: m itself
+};
 int rope_table_entries(int T, int gh, int gw, int dh);
-hipError_t launch_rope_table(int T, int gh, int gw, int dh, double base, float2* tab, hipStream_t stream);
-hipError_t launch_qk_norm_rope(bf16_t* z, int64_t ldz, int M, int D, const float* g, float eps,
-                               const int32_t* rows, const float2* tab, int L, int T, int gh, int gw, int dh,
-                               hipStream_t stream);
-hipError_t launch_vec_shift(const float* a, float beta, float* out, int n, hipStream_t stream);
+hipError_t launch_wan_constants(int T, int gh, int gw, int dh, double base, float2* tab, const float* g3, float* ones,
+                                float* g3m1, int D, hipStream_t stream);
+hipError_t launch_qk_norm_rope(const QkRows& a, const QkRows& b, int D, float eps, const float2* tab, int L, int T,
+                               int gh, int gw, int dh, hipStream_t stream);
 
 hipError_t launch_modln_input(int dtype_bf16, const void* x, int M, int D, const float* shift,
                               const float* scale, float eps, void* out, hipStream_t stream);

@@ -1,7 +1,7 @@
 // The Wan-style block extras on the restricted-query path: qk RMSNorm with 3D
 // rotary position embedding, applied in place to the q and k projections, the
-// rotary angle table it reads, and a small vector kernel for the constant
-// operands of the cross-attention sub-layer.
+// rotary angle table it reads, made with the constant operands of the
+// cross-attention sub-layer.
 //
 // qk_norm_rope_rows: one wave per row, the row held in registers as raw
 //   16-byte vectors (all loads issued before the first is used); the RMSNorm
@@ -12,8 +12,9 @@
 //   is rotated by the angle of its axis: the first nt pairs by the token's
 //   frame t, the next nr by its grid row r, the last nc by its grid column c.
 //   An 8-element chunk holds four whole pairs, so a lane rotates its own data.
-// rope_table: (cos, sin) of p * base^(-j / n) for every axis position p and
-//   pair j < n of the axis, computed in fp64 and stored as fp32 pairs.
+// wan_constants: (cos, sin) of p * base^(-j / n) for every axis position p and
+//   pair j < n of the axis, computed in fp64 and stored as fp32 pairs; and the
+//   constant operands.
 #include <math.h>
 
 #include <type_traits>
@@ -39,11 +40,22 @@ int rope_table_entries(int T, int gh, int gw, int dh) {
   return T * nt + gh * nr + gw * nc;
 }
 
+// All constants of a block call in one launch (three of 4.5 us before): the
+// table's entries, then per channel the unit gate of the cross-attention
+// output and the affine weight of its LN less one.
 __global__ void __launch_bounds__(256)
-rope_table(int T, int gh, int gw, int nt, int nr, int nc, double base, float2* __restrict__ tab) {
+wan_constants(int T, int gh, int gw, int nt, int nr, int nc, double base, float2* __restrict__ tab,
+              const float* __restrict__ g3, float* __restrict__ ones, float* __restrict__ g3m1, int D) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   const int e_t = T * nt, e_r = gh * nr, e_c = gw * nc;
-  if (i >= e_t + e_r + e_c) return;
+  if (i >= e_t + e_r + e_c) {
+    const int ch = i - (e_t + e_r + e_c);
+    if (ch < D) {
+      ones[ch] = 1.0f;
+      g3m1[ch] = g3[ch] - 1.0f;
+    }
+    return;
+  }
   int p, j, n;
   if (i < e_t) {
     p = i / nt, j = i % nt, n = nt;
@@ -66,16 +78,26 @@ struct RopeGeom {
 
 // MAXC > 0: the row stays in registers (D <= 512 MAXC); MAXC == 0 reads it twice.
 // STAGE: the workgroup first copies the RMSNorm weight and the angle table to
-// LDS and each wave then loops over rows (row = 4 blockIdx.x + wave, in steps
-// of 4 gridDim.x): read from L2 for every row, the weight (fp32) and the
+// LDS and each wave then loops over rows (row = 4 wg + wave of its side, in steps
+// of four times the side's workgroups): read from L2 for every row, the weight (fp32) and the
 // table entries moved four times the row's own bytes through the load path.
 // SAME: a lane's chunks, 512 elements apart, hold the same pairs of their
 // heads (the head size divides 512), so the four angles are read once a row.
+// The q and the k rows go in one launch: workgroups [0, na) take a, the others
+// b, in proportion to their rows: 3900 q and 15600 k rows of 1536 take 29 us
+// where two launches took 12 + 22, 3900 and 1024 rows 9 us (8 + 5).
 template <int MAXC, bool STAGE, bool SAME = false>
 __global__ void __launch_bounds__(kWanThreads)
-qk_norm_rope_rows(bf16_t* __restrict__ z, int64_t ldz, int M, int D, const float* __restrict__ g, float eps,
-                  const int32_t* __restrict__ rows, RopeGeom geo) {
+qk_norm_rope_rows(QkRows a, QkRows b, int na, int D, float eps, RopeGeom geo) {
   extern __shared__ float4 qkn_lds[];
+  const bool is_a = static_cast<int>(blockIdx.x) < na;  // uniform
+  bf16_t* __restrict__ const z = is_a ? a.z : b.z;
+  const float* __restrict__ const g = is_a ? a.g : b.g;
+  const int32_t* __restrict__ const rows = is_a ? a.rows : b.rows;
+  const int64_t ldz = is_a ? a.ldz : b.ldz;
+  const int M = is_a ? a.M : b.M;
+  const int wg = static_cast<int>(blockIdx.x) - (is_a ? 0 : na);
+  const int nwg = is_a ? na : static_cast<int>(gridDim.x) - na;
   const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
   const int off_r = geo.T * geo.nt, off_c = off_r + geo.gh * geo.nr;  // first entries of the row and column axes
   float* gl = reinterpret_cast<float*>(qkn_lds);                     // [D] weight (STAGE)
@@ -91,8 +113,8 @@ qk_norm_rope_rows(bf16_t* __restrict__ z, int64_t ldz, int M, int D, const float
   auto inv_rms = [&](float ss) __attribute__((always_inline)) {
     return __frcp_rn(__fsqrt_rn(__fadd_rn(__fdiv_rn(ss, static_cast<float>(D)), eps)));
   };
-  const int64_t step = STAGE ? static_cast<int64_t>(gridDim.x) * kWanWaves : static_cast<int64_t>(M);
-  for (int64_t m = static_cast<int64_t>(blockIdx.x) * kWanWaves + wave; m < M; m += step) {
+  const int64_t step = STAGE ? static_cast<int64_t>(nwg) * kWanWaves : static_cast<int64_t>(M);
+  for (int64_t m = static_cast<int64_t>(wg) * kWanWaves + wave; m < M; m += step) {
     bf16_t* zr = z + m * ldz;
     int t = 0, r = 0, c = 0;
     if (geo.tab != nullptr) {
@@ -204,42 +226,43 @@ qk_norm_rope_rows(bf16_t* __restrict__ z, int64_t ldz, int M, int D, const float
   }
 }
 
-// out[i] = (a ? a[i] : 0) + beta
-__global__ void __launch_bounds__(256)
-vec_shift(const float* __restrict__ a, float beta, float* __restrict__ out, int n) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) out[i] = (a != nullptr ? a[i] : 0.0f) + beta;
-}
-
-hipError_t launch_rope_table(int T, int gh, int gw, int dh, double base, float2* tab, hipStream_t stream) {
+hipError_t launch_wan_constants(int T, int gh, int gw, int dh, double base, float2* tab, const float* g3, float* ones,
+                                float* g3m1, int D, hipStream_t stream) {
   int nt, nr, nc;
   rope_split(dh, &nt, &nr, &nc);
-  const int n = T * nt + gh * nr + gw * nc;
-  return ECHO_LAUNCH("rope_table", rope_table, dim3((n + 255) / 256), dim3(256), 0, stream, T, gh, gw, nt, nr, nc,
-                     base, tab);
+  const int n = T * nt + gh * nr + gw * nc + D;
+  return ECHO_LAUNCH("wan_constants", wan_constants, dim3((n + 255) / 256), dim3(256), 0, stream, T, gh, gw, nt, nr,
+                     nc, base, tab, g3, ones, g3m1, D);
 }
 
-hipError_t launch_qk_norm_rope(bf16_t* z, int64_t ldz, int M, int D, const float* g, float eps,
-                               const int32_t* rows, const float2* tab, int L, int T, int gh, int gw, int dh,
-                               hipStream_t stream) {
-  if (M <= 0) return hipSuccess;
+hipError_t launch_qk_norm_rope(const QkRows& a, const QkRows& b, int D, float eps, const float2* tab, int L, int T,
+                               int gh, int gw, int dh, hipStream_t stream) {
+  if (a.M <= 0 && b.M <= 0) return hipSuccess;
   RopeGeom geo{tab, L, gh, gw, T, 0, 0, 0, dh};
   rope_split(dh, &geo.nt, &geo.nr, &geo.nc);
-  const dim3 grid(static_cast<unsigned>((M + kWanWaves - 1) / kWanWaves));
+  const int wa = (a.M + kWanWaves - 1) / kWanWaves, wb = (b.M + kWanWaves - 1) / kWanWaves;
+  const dim3 grid(static_cast<unsigned>(wa + wb));
   const int per_lane = (D / 8 + kWave - 1) / kWave;
   // weight and table in LDS when they fit four workgroups per CU
   const size_t ntab = tab != nullptr ? size_t(T) * geo.nt + size_t(gh) * geo.nr + size_t(gw) * geo.nc : 0;
   const size_t lds = sizeof(float) * size_t(D) + sizeof(float2) * ntab;
   if (lds <= 40960) {
-    const unsigned cap = 4u * static_cast<unsigned>(device_cu_count());
-    const dim3 grid_s(grid.x < cap ? grid.x : cap);
+    // as many workgroups as are resident together, each side its share by rows (at least one if it has any)
+    const int cap = 4 * device_cu_count();
+    int na = wa, nb = wb;
+    if (wa + wb > cap) {
+      na = static_cast<int>((int64_t(cap) * wa + (wa + wb) / 2) / (wa + wb));
+      na = wa > 0 && na < 1 ? 1 : wb > 0 && na > cap - 1 ? cap - 1 : na;
+      nb = cap - na;
+    }
+    const dim3 grid_s(static_cast<unsigned>(na + nb));
 #define ECHO_QKS_CASE(MC)                                                                                      \
   if (per_lane <= MC) {                                                                                        \
     if (tab == nullptr || 512 % dh == 0)                                                                       \
       return ECHO_LAUNCH("qk_norm_rope", (qk_norm_rope_rows<MC, true, true>), grid_s, dim3(kWanThreads), lds,   \
-                         stream, z, ldz, M, D, g, eps, rows, geo);                                            \
+                         stream, a, b, na, D, eps, geo);                                                       \
     return ECHO_LAUNCH("qk_norm_rope", (qk_norm_rope_rows<MC, true, false>), grid_s, dim3(kWanThreads), lds,    \
-                       stream, z, ldz, M, D, g, eps, rows, geo);                                              \
+                       stream, a, b, na, D, eps, geo);                                                         \
   }
     ECHO_QKS_CASE(1)
     ECHO_QKS_CASE(2)
@@ -251,8 +274,8 @@ hipError_t launch_qk_norm_rope(bf16_t* z, int64_t ldz, int M, int D, const float
   }
 #define ECHO_QKN_CASE(MC)                                                                                   \
   if (per_lane <= MC)                                                                                       \
-    return ECHO_LAUNCH("qk_norm_rope", (qk_norm_rope_rows<MC, false>), grid, dim3(kWanThreads), 0, stream, z, ldz, \
-                       M, D, g, eps, rows, geo);
+    return ECHO_LAUNCH("qk_norm_rope", (qk_norm_rope_rows<MC, false>), grid, dim3(kWanThreads), 0, stream, a, b, wa, \
+                       D, eps, geo);
   ECHO_QKN_CASE(1)
   ECHO_QKN_CASE(2)
   ECHO_QKN_CASE(4)
@@ -260,12 +283,8 @@ hipError_t launch_qk_norm_rope(bf16_t* z, int64_t ldz, int M, int D, const float
   ECHO_QKN_CASE(10)
   ECHO_QKN_CASE(16)
 #undef ECHO_QKN_CASE
-  return ECHO_LAUNCH("qk_norm_rope", (qk_norm_rope_rows<0, false>), grid, dim3(kWanThreads), 0, stream, z, ldz, M,
-                     D, g, eps, rows, geo);
-}
-
-hipError_t launch_vec_shift(const float* a, float beta, float* out, int n, hipStream_t stream) {
-  return ECHO_LAUNCH("vec_shift", vec_shift, dim3((n + 255) / 256), dim3(256), 0, stream, a, beta, out, n);
+  return ECHO_LAUNCH("qk_norm_rope", (qk_norm_rope_rows<0, false>), grid, dim3(kWanThreads), 0, stream, a, b, wa, D,
+                     eps, geo);
 }
 
 }  // namespace echo

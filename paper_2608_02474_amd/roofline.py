@@ -67,10 +67,10 @@ def wan_block_work(B: int, L: int, K: int, D: int, F: int, Lc: int, b: int):
     """Work per launch of the Wan-style block's kernels for a batch of B
     elements with K selected tokens each and Lc context rows: {name prefix:
     (amount per launch, kind)}.  The GEMMs run once over the whole batch;
-    attention runs once per element; qk_norm_rope runs four times (q, k, the
-    cross-attention q and k), given as the mean of the four."""
+    attention runs once per element; qk_norm_rope runs twice (q and k, the
+    cross-attention q and k), given as the mean of the two."""
     n = B * K
-    norm_bytes = (2 * n + B * L + B * Lc) * D * 2 * b // 4
+    norm_bytes = (2 * n + B * L + B * Lc) * D * 2 * b // 2
     return {
         "qk_norm_rope": (norm_bytes, "byte"),
         "gemm_qkvc": (2 * n * D * D + 4 * B * Lc * D * D, "flop"),

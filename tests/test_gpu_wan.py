@@ -67,6 +67,23 @@ def test_wan_block_all_tokens_one_element():
     check_block(got, OW.block_partial(p, x, ctx, idx, w.H, w.grid), w.dtype, w.name)
 
 
+@pytest.mark.parametrize("grid,K", [((40, 70), 1), ((40, 70), 8399), ((1, 2800), 3)])
+def test_wan_block_norm_shares(grid, K):
+    """The q and the k rows share a launch: a side of one row beside thousands
+    (one workgroup at least), both sides large, and a rotary table too large
+    for on-chip memory; the oracle on sampled rows."""
+    w = SMALL.with_(name=f"wan_share_{grid[0]}x{grid[1]}_k{K}", grid=grid, seed=43)
+    p = synth.make_wan_block_weights(w)
+    _, x = synth.make_latents(w)
+    ctx = synth.make_context(w, 3)
+    rng = np.random.default_rng(K)
+    idx = np.sort(rng.choice(w.L, K, replace=False))
+    say(f"wan block {w.name} L={w.L} (GPU)")
+    got = _run(w, p, [x], [ctx], [idx])[0]
+    rows = np.unique(np.concatenate([[0, K - 1], rng.choice(K, min(K, 14), replace=False)]))
+    check_block(got[rows], OW.block_partial(p, x, ctx, idx[rows], w.H, w.grid), w.dtype, w.name)
+
+
 def test_wan_block_full_size_sampled():
     """The 32760-token shape, B = 2 with their own contexts (512 tokens) and
     selections, in the benchmark's launch configuration; the oracle computes
