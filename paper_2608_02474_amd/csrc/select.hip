@@ -24,6 +24,7 @@
 // compare for the keys outside the digit in the others; a wave's counts in its lanes).
 // Four passes of 8 bits with a leader election per 64 keys and a count written
 // per (round, wave) took 36.5 us at 32760 keys, this form 24.7; at 75600 keys 147 and 62.6.
+// select_small: saliency, step-level sum and selection of few tokens, one launch.
 // select_segments: the same selection per anchor segment, one workgroup per
 //   segment (the two-stage form: anchor segments, then min(k, N) tokens each).
 // anchor_select: the anchor segments (top-k of per-segment keys, or evenly
@@ -476,6 +477,109 @@ anchor_select(const float* __restrict__ keys, int T, int k, int mode, uint8_t* _
   }
 }
 
+// ---- a selection of few tokens in one launch.  Two dependent launches and a
+// digit-wise selection made for thousands of keys are all latency here: one
+// workgroup takes the saliency of every row (a wave per row, kSmallRows rows'
+// loads together, a chunk of 8 elements per lane: D <= 512), keeps the keys in
+// LDS and ranks each by counting the keys before it, one thread per key; the
+// step-level sum adds the same pairs in the same order as the kernels above.
+// A call of 32 or 64 tokens takes 13 us (two launches 16); with more than four
+// rows a wave the rows follow one another, and 192 tokens take 19 us (16), 256
+// 24, hence the limit.
+constexpr int kSmallTokens = 64, kSmallD = 512;
+constexpr int kSmallRows = kSmallTokens / kSelWaves;
+
+template <typename T>
+__global__ void __launch_bounds__(kSelThreads)
+select_small(const T* __restrict__ x, const T* __restrict__ xref, const float* __restrict__ fw, int L, int N, int D,
+             double xi, int k, int threshold_mode, float threshold, float* __restrict__ s_out,
+             int32_t* __restrict__ idx, uint8_t* __restrict__ mask, int32_t* __restrict__ n_sel,
+             double* __restrict__ step_delta) {
+  __shared__ __attribute__((aligned(16))) uint32_t keys[kSmallTokens];
+  __shared__ double rn[kSmallTokens], rd[kSmallTokens];
+  __shared__ double gn[kSmallTokens / 4], gd[kSmallTokens / 4];
+  const int tid = threadIdx.x, lane = tid % kWave;
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  if (tid < kSmallTokens) {
+    keys[tid] = 0u;  // "no key" past L
+    rn[tid] = rd[tid] = 0.0;
+  }
+  __syncthreads();
+  const int nch = D / 8, cc = lane < nch ? lane : nch - 1;
+  Raw8<T> ra[kSmallRows], rb[kSmallRows];
+#pragma unroll
+  for (int u = 0; u < kSmallRows; ++u) {
+    const int r = wave + u * kSelWaves;
+    const int64_t row = r < L ? r : L - 1;
+    ra[u].load(x + row * D + cc * 8);
+    rb[u].load(xref + row * D + cc * 8);
+  }
+#pragma unroll
+  for (int u = 0; u < kSmallRows; ++u) {
+    const int r = wave + u * kSelWaves;
+    if (r >= L) break;  // uniform
+    float fa[8], fb[8];
+    ra[u].unpack(fa);
+    rb[u].unpack(fb);
+    double num = 0.0, den = 0.0;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const double da = fa[j], db = fb[j];
+      num += fabs(da - db);
+      den += fabs(db);
+    }
+    num = wave_sum(lane < nch ? num : 0.0);
+    den = wave_sum(lane < nch ? den : 0.0);
+    if (lane == 0) {
+      const double delta = num / (den + xi);
+      const float s = __double2float_rn(static_cast<double>(fw[r / N]) * delta);
+      s_out[r] = s;
+      keys[r] = rank_key(s);
+      rn[r] = num;
+      rd[r] = den;
+    }
+  }
+  __syncthreads();
+  if (wave == 0) {  // a key per lane
+    const uint32_t mine = keys[lane];
+    bool sel;
+    if (threshold_mode) {
+      sel = mine > rank_key(threshold);
+    } else {
+      int before = 0;
+#pragma unroll
+      for (int u = 0; u < kSmallTokens / 4; ++u) {
+        const uint4 q = reinterpret_cast<const uint4*>(keys)[u];
+        const int b = 4 * u;
+        before += (q.x > mine || (q.x == mine && b < lane)) ? 1 : 0;
+        before += (q.y > mine || (q.y == mine && b + 1 < lane)) ? 1 : 0;
+        before += (q.z > mine || (q.z == mine && b + 2 < lane)) ? 1 : 0;
+        before += (q.w > mine || (q.w == mine && b + 3 < lane)) ? 1 : 0;
+      }
+      sel = before < k;
+    }
+    sel = sel && lane < L;
+    const uint64_t bsel = __ballot(sel);
+    if (lane < L) {
+      mask[lane] = sel ? 1 : 0;
+      if (sel) idx[lanes_below(bsel)] = lane;
+    }
+    if (lane == 0) *n_sel = static_cast<int32_t>(__popcll(bsel));
+    if (lane < kSmallTokens / 4) {  // the sums of four rows, as a saliency workgroup leaves them
+      double a = rn[4 * lane], b = rd[4 * lane];
+#pragma unroll
+      for (int j = 1; j < 4; ++j) {
+        a += rn[4 * lane + j];
+        b += rd[4 * lane + j];
+      }
+      gn[lane] = a;
+      gd[lane] = b;
+    }
+  }
+  __syncthreads();
+  if (step_delta != nullptr) step_delta_block(gn, gd, (L + 3) / 4, xi, step_delta);
+}
+
 // workgroups of the saliency pass, each of which leaves one pair of sums
 static int sal_parts(int L) { return (L + (kSalThreads / kWave) - 1) / (kSalThreads / kWave); }
 
@@ -559,6 +663,15 @@ hipError_t launch_select(int dtype_bf16, const void* x, const void* xref, const 
                          int D, double xi, int k, int threshold_mode, float threshold, float* s,
                          double* num, double* den, int32_t* idx, uint8_t* mask, int32_t* n_sel,
                          double* step_delta, hipStream_t stream) {
+  if (L <= kSmallTokens && D <= kSmallD) {
+    if (dtype_bf16)
+      return ECHO_LAUNCH("select_small", select_small<bf16_t>, dim3(1), dim3(kSelThreads), 0, stream,
+                         static_cast<const bf16_t*>(x), static_cast<const bf16_t*>(xref), fw, L, N, D, xi, k,
+                         threshold_mode, threshold, s, idx, mask, n_sel, step_delta);
+    return ECHO_LAUNCH("select_small", select_small<float>, dim3(1), dim3(kSelThreads), 0, stream,
+                       static_cast<const float*>(x), static_cast<const float*>(xref), fw, L, N, D, xi, k,
+                       threshold_mode, threshold, s, idx, mask, n_sel, step_delta);
+  }
   // the step-level sum runs beside the selection, in the same launch
   const hipError_t e = launch_saliency(dtype_bf16, x, xref, fw, L, N, D, xi, s, num, den, nullptr, stream);
   if (e != hipSuccess) return e;

@@ -82,6 +82,40 @@ def test_topk_edges(L, kind):
         assert np.array_equal(mask, m), (mode, v)
 
 
+@pytest.mark.parametrize("T,N,D", [(1, 1, 8), (3, 1, 512), (1, 5, 72), (2, 16, 64), (4, 16, 512), (1, 64, 504),
+                                   (3, 21, 128), (5, 13, 64), (2, 8, 520)])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_select_of_few_tokens_is_the_two_passes(T, N, D, dtype):
+    """The one-launch selection of few tokens against the saliency pass and the
+    digit-wise selection: the same bits, with equal rows (ties), rows without
+    change, a zero reference and non-finite values."""
+    L = T * N
+    rng = np.random.default_rng(L * 1000 + D)
+    x, xr = (rng.standard_normal((2, L, D)) * 0.7).astype(np.float32)
+    for r in range(0, L, 3):
+        x[r], xr[r] = x[0], xr[0]
+    x[1::7] = xr[1::7]
+    xr[2::11] = 0.0
+    if L > 8:
+        x[5, 0], x[6, D - 1], xr[8, 3] = np.nan, np.inf, np.inf
+    dt = tdtype(dtype)
+    X, XR, fw = up(x, dt), up(xr, dt), up(np.linspace(0.0, 1.0, T).astype(np.float32))
+    half = api.saliency(X, XR, fw, N)
+    thr = float(np.nanmedian(down(half.saliency)))
+    for mode, v in [("k", k) for k in sorted({0, 1, L // 2, L})] + [("threshold", thr), ("threshold", -1.0)]:
+        say(f"select of {L} tokens D={D} {dtype} {mode}={v}")
+        whole = api.select(X, XR, fw, N, **{mode: v})
+        api.topk(half, N, D, dt, **{mode: v})
+        torch.cuda.synchronize()
+        n = int(half.n_sel_dev.item())
+        assert int(whole.n_sel_dev.item()) == n, (mode, v)
+        for name in ("mask", "saliency", "step_delta", "idx"):
+            a, b = down(getattr(whole, name)), down(getattr(half, name))
+            if name == "idx":
+                a, b = a[:n], b[:n]
+            assert np.array_equal(a.view(np.uint8), b.view(np.uint8)), (mode, v, name)
+
+
 def _trajectory(w, steps, seed=7):
     rng = np.random.default_rng(seed)
     from oracle.cache import cast_act
