@@ -4,8 +4,8 @@
 // Kernel 1 (energy_frames): one workgroup per (segment, STFT frame), in fp64.
 // For a power-of-two n_fft, an in-place FFT in LDS; for any other even n_fft,
 // each thread evaluates whole one-sided bins k directly from the DFT sum over a
-// full-period twiddle table.  |X_k|^2 and each bin's band go to LDS, and one
-// wave per band sums its bins.  Both stay within fp64 rounding of the
+// full-period twiddle table.  |X_k|^2 and each band's range of bins go to LDS,
+// and one wave per band sums its bins.  Both stay within fp64 rounding of the
 // definition.
 // Kernel 2 (energy_reduce): one workgroup sums the per-frame band energies of
 // each (segment, band) in frame order (one thread each), then each segment's
@@ -30,15 +30,22 @@ __device__ __forceinline__ int band_of_bin(int k, int n_fft, int sr, int n_bands
   return b < n_bands - 1 ? b : n_bands - 1;
 }
 
-// Per-band sums of the bin powers, one wave per band (lanes take bins
-// lane, lane + 64, ...; fp64 throughout).
-__device__ __forceinline__ void band_sums(const double* pw, const int* bandof, int nbins, int n_bands,
-                                          double* __restrict__ out) {
+// Bands are ranges of bins: first[band] = its first bin, first[n_bands] = nbins
+// (bandof ascends and ends at n_bands - 1).
+__device__ __forceinline__ void band_starts(const int* bandof, int nbins, int n_bands, int* first) {
+  for (int k = threadIdx.x; k < nbins; k += blockDim.x)
+    for (int band = k > 0 ? bandof[k - 1] + 1 : 0; band <= bandof[k]; ++band) first[band] = k;
+  if (threadIdx.x == 0) first[n_bands] = nbins;
+}
+
+// Per-band sums of the bin powers, one wave per band (lane l takes bins l, l +
+// 64, ... of the band; fp64 throughout).
+__device__ __forceinline__ void band_sums(const double* pw, const int* first, int n_bands, double* __restrict__ out) {
   const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave, nw = blockDim.x / kWave;
   for (int band = wave; band < n_bands; band += nw) {
     double acc = 0.0;
-    for (int k = lane; k < nbins; k += kWave)
-      if (bandof[k] == band) acc += pw[k];
+    const int k1 = first[band + 1];
+    for (int k = first[band] + lane; k < k1; k += kWave) acc += pw[k];
     acc = wave_sum(acc);
     if (lane == 0) out[band] = acc;
   }
@@ -99,13 +106,9 @@ energy_frames_fft(const float* __restrict__ audio, int64_t n_samples, int T, int
     z[j] = make_double2(v0 + v1, 0.0);
     z[j + half] = make_double2(d * w.x, d * w.y);
   }
-  if (tid == 0) {
-    bandof[half] = n_bands - 1;  // half the sampling rate: the top of the last band
-    first[n_bands] = half + 1;
-  }
+  if (tid == 0) bandof[half] = n_bands - 1;  // half the sampling rate: the top of the last band
   __syncthreads();
-  for (int k = tid; k <= half; k += kFftThreads)
-    for (int band = k > 0 ? bandof[k - 1] + 1 : 0; band <= bandof[k]; ++band) first[band] = k;
+  band_starts(bandof, half + 1, n_bands, first);
   int left = log2n - 1;  // stages still to do, each on blocks of 2^left
   if (left & 1) {
     const int h = 1 << (left - 1);
@@ -145,25 +148,36 @@ energy_frames_fft(const float* __restrict__ audio, int64_t n_samples, int T, int
     }
     __syncthreads();
   }
-  const int wave = tid / kWave, lane = tid % kWave;
-  for (int band = wave; band < n_bands; band += kFftThreads / kWave) {
-    double acc = 0.0;
-    const int k1 = first[band + 1];
-    for (int k = first[band] + lane; k < k1; k += kWave) acc += pw[k];
-    acc = wave_sum(acc);
-    if (lane == 0) out[band] = acc;
-  }
+  band_sums(pw, first, n_bands, out);
 }
 
+// groups of threads that share a bin's terms
+__host__ __device__ __forceinline__ int dft_groups(int nbins) {
+  return nbins <= kFrameThreads / 4 ? 4 : nbins <= kFrameThreads / 2 ? 2 : 1;
+}
+
+// Any other even n_fft: the DFT sum of each one-sided bin.  Samples n and n_fft -
+// n share their cosine and, but for the sign, their sine, so that a bin takes
+// half the terms (sums with the cosines, differences with the sines); threads
+// that bins leave idle share the terms.  The table reads (a bank conflict or
+// two each) and fp64 multiply-adds bound it.  A call with n_fft 400 and 81000
+// samples 41 -> 22 us, 480000 samples 185 -> 121, n_fft 1000 314 -> 211 (all
+// terms by one thread per bin -> this).
 __global__ void __launch_bounds__(kFrameThreads)
 energy_frames(const float* __restrict__ audio, int64_t n_samples, int T, int n_fft, int hop,
               int n_bands, int sr, int max_frames, double* __restrict__ part) {
   extern __shared__ double lds[];
-  double* xw = lds;                 // [n_fft] windowed frame
+  double* xw = lds;                 // [n_fft] windowed frame; then sums at n, differences at n_fft - n
   double* tc = lds + n_fft;         // [n_fft] cos(2 pi m / n_fft)
   double* ts = lds + 2 * n_fft;     // [n_fft] sin(2 pi m / n_fft)
   double* pw = lds + 3 * n_fft;     // [n_fft/2 + 1] |X_k|^2
-  int* bandof = reinterpret_cast<int*>(lds + 3 * n_fft + n_fft / 2 + 1);  // [n_fft/2 + 1] band of bin k
+  const int tid = threadIdx.x, half = n_fft / 2, nbins = half + 1;
+  // G groups of S threads: a bin per thread of a group, the terms divided among the groups
+  const int G = dft_groups(nbins), S = kFrameThreads / G;
+  double* pre = pw + nbins;          // [kFrameThreads] partial sums of the groups (G > 1)
+  double* pim = pre + kFrameThreads;
+  int* bandof = reinterpret_cast<int*>(G > 1 ? pim + kFrameThreads : pre);  // [nbins] band of bin k
+  int* first = bandof + nbins;                                              // [n_bands + 1] first bin of a band
   const int t = blockIdx.y, f = blockIdx.x;
   const int64_t a = (static_cast<int64_t>(t) * n_samples) / T;
   const int64_t b = (static_cast<int64_t>(t + 1) * n_samples) / T;
@@ -175,50 +189,72 @@ energy_frames(const float* __restrict__ audio, int64_t n_samples, int T, int n_f
     return;
   }
   const int64_t start = a + static_cast<int64_t>(f) * hop;
-  for (int n = threadIdx.x; n < n_fft; n += blockDim.x) {
-    const double w = 0.5 - 0.5 * cospi(2.0 * n / n_fft);      // periodic Hann
+  for (int n = tid; n < n_fft; n += kFrameThreads) {
     const int64_t s = start + n;
-    const double v = (s < b) ? static_cast<double>(audio[s]) : 0.0;  // zero-pad short segments
-    xw[n] = w * v;
+    const float smp = audio[s < b ? s : b - 1];
     double sn, cs;
     sincospi(2.0 * n / n_fft, &sn, &cs);
     tc[n] = cs;
     ts[n] = sn;
+    // periodic Hann; a short segment is padded with zeros
+    xw[n] = s < b ? (0.5 - 0.5 * cs) * static_cast<double>(smp) : 0.0;
   }
+  for (int k = tid; k < nbins; k += kFrameThreads) bandof[k] = k < half ? band_of_bin(k, n_fft, sr, n_bands) : n_bands - 1;
   __syncthreads();
-  const int nbins = n_fft / 2 + 1;
-  for (int k = threadIdx.x; k < nbins; k += blockDim.x) {
-    // four independent partial sums over n = 4j + u, so that four twiddle
-    // reads and FMA chains are in flight at once (an even n_fft that is not
-    // a multiple of 4 leaves two terms for the tail)
+  for (int n = 1 + tid; n < half; n += kFrameThreads) {
+    const double u = xw[n], v = xw[n_fft - n];
+    xw[n] = u + v;
+    xw[n_fft - n] = u - v;
+  }
+  band_starts(bandof, nbins, n_bands, first);
+  __syncthreads();
+  const int g = tid / S;  // terms 1 .. half - 1
+  const int per = (half - 1 + G - 1) / G;
+  const int n0 = 1 + g * per, n1 = n0 + per < half ? n0 + per : half;
+  for (int k0 = 0; k0 < nbins; k0 += S) {
+    const int k = k0 + tid % S;
+    // four independent partial sums, so that four twiddle reads and FMA chains
+    // are in flight at once
     double re[4] = {0.0, 0.0, 0.0, 0.0}, im[4] = {0.0, 0.0, 0.0, 0.0};
-    int m[4];  // (k * n) mod n_fft for the four current n, advanced by 4k
+    if (k < nbins) {
+      int m[4];  // (k * n) mod n_fft for the four current n, advanced by 4k
 #pragma unroll
-    for (int u = 0; u < 4; ++u) m[u] = (k * u) % n_fft;
-    const int step = (4 * k) % n_fft;
-    int n = 0;
-    for (; n + 4 <= n_fft; n += 4) {
+      for (int u = 0; u < 4; ++u) m[u] = (k * (n0 + u)) % n_fft;
+      const int step = (4 * k) % n_fft;
+      int n = n0;
+      for (; n + 4 <= n1; n += 4) {
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const double x = xw[n + u];
-        re[u] = fma(x, tc[m[u]], re[u]);
-        im[u] = fma(-x, ts[m[u]], im[u]);
-        m[u] += step;
-        if (m[u] >= n_fft) m[u] -= n_fft;
+        for (int u = 0; u < 4; ++u) {
+          re[u] = fma(xw[n + u], tc[m[u]], re[u]);
+          im[u] = fma(xw[n_fft - n - u], ts[m[u]], im[u]);
+          m[u] += step;
+          if (m[u] >= n_fft) m[u] -= n_fft;
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < 3; ++u)
+        if (n + u < n1) {
+          re[u] = fma(xw[n + u], tc[m[u]], re[u]);
+          im[u] = fma(xw[n_fft - n - u], ts[m[u]], im[u]);
+        }
+    }
+    double r = (re[0] + re[1]) + (re[2] + re[3]), i = (im[0] + im[1]) + (im[2] + im[3]);
+    if (G > 1) {  // uniform; S >= nbins, one pass
+      pre[tid] = r;
+      pim[tid] = i;
+      __syncthreads();
+      for (int h = 1; g == 0 && h < G; ++h) {
+        r += pre[tid + h * S];
+        i += pim[tid + h * S];
       }
     }
-    for (int u = 0; n + u < n_fft; ++u) {
-      const double x = xw[n + u];
-      re[u] = fma(x, tc[m[u]], re[u]);
-      im[u] = fma(-x, ts[m[u]], im[u]);
+    if (g == 0 && k < nbins) {
+      r += xw[0] + ((k & 1) ? -xw[half] : xw[half]);
+      pw[k] = r * r + i * i;
     }
-    const double r = (re[0] + re[1]) + (re[2] + re[3]);
-    const double i = (im[0] + im[1]) + (im[2] + im[3]);
-    pw[k] = r * r + i * i;
-    bandof[k] = band_of_bin(k, n_fft, sr, n_bands);
   }
   __syncthreads();
-  band_sums(pw, bandof, nbins, n_bands, out);
+  band_sums(pw, first, n_bands, out);
 }
 
 // One workgroup: three dependent steps, so that the memory in flight and the
@@ -299,7 +335,8 @@ hipError_t launch_energy(const float* audio, int64_t n_samples, int T, int sr, i
     e = ECHO_LAUNCH("energy_frames", energy_frames_fft, dim3(mf, T), dim3(kFftThreads), lds, stream, audio,
                     n_samples, T, n_fft, log2n, hop, n_bands, sr, mf, part);
   } else {
-    const size_t lds = sizeof(double) * (3 * n_fft + n_fft / 2 + 1) + sizeof(int) * (n_fft / 2 + 1);
+    const int sums = dft_groups(n_fft / 2 + 1) > 1 ? 2 * kFrameThreads : 0;
+    const size_t lds = sizeof(double) * (3 * n_fft + n_fft / 2 + 1 + sums) + sizeof(int) * (n_fft / 2 + 2 + n_bands);
     e = ECHO_LAUNCH("energy_frames", energy_frames, dim3(mf, T), dim3(kFrameThreads), lds, stream, audio,
                     n_samples, T, n_fft, hop, n_bands, sr, mf, part);
   }

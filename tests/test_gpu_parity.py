@@ -65,10 +65,13 @@ def test_energy_other_stft_sizes(n_fft, hop, bands):
 
 @pytest.mark.parametrize("n_fft,hop,bands,T,n", [(16, 5, 64, 3, 900), (32, 16, 5, 2, 700), (64, 9, 1, 1, 3000),
                                                  (1024, 300, 9, 4, 30000), (16, 16, 16, 300, 9000),
-                                                 (2048, 1500, 64, 33, 69300), (512, 512, 8, 7, 7)])
+                                                 (2048, 1500, 64, 33, 69300), (512, 512, 8, 7, 7),
+                                                 (18, 18, 64, 2, 500), (254, 100, 8, 3, 9000), (258, 60, 4, 1, 254),
+                                                 (400, 160, 8, 5, 20000), (510, 200, 8, 2, 5000),
+                                                 (514, 200, 8, 2, 5000), (2046, 900, 64, 3, 9000)])
 def test_energy_fft_stages_and_sums(n_fft, hop, bands, T, n):
-    """Odd and even numbers of stages, empty bands, more frames than the sum
-    keeps in flight, and more band sums and segments than it holds on chip.
+    """Odd and even numbers of stages, the direct sum with its terms in 4, 2 and
+    1 parts, empty bands, more frames than the sum keeps in flight, and more band sums and segments than it holds on chip.
     The sums are in 64 bits, so that the fp32 results differ by rounding
     (6e-8) only."""
     say(f"energy n_fft={n_fft} hop={hop} bands={bands} T={T} n={n}")
