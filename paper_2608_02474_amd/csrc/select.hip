@@ -24,6 +24,10 @@
 // compare for the keys outside the digit in the others; a wave's counts in its lanes).
 // Four passes of 8 bits with a leader election per 64 keys and a count written
 // per (round, wave) took 36.5 us at 32760 keys, this form 24.7; at 75600 keys 147 and 62.6.
+// Adds of many lanes to one address follow one another (2 cycles each), which
+// matters where most keys tie, as they do over silent frames and unchanged
+// tokens: 32760 equal keys took 76 us with a plain add per key, 25 with the
+// rules at the digits below (39 with the four passes).
 // select_small: saliency, step-level sum and selection of few tokens, one launch.
 // select_segments: the same selection per anchor segment, one workgroup per
 //   segment (the two-stage form: anchor segments, then min(k, N) tokens each).
@@ -168,7 +172,7 @@ struct TopkLds {
   uint32_t h1[2048 * 4];  // digit 1, four copies side by side (a lane uses copy lane % 4): the keys of a
                           // step lie in a few octaves, so that most lanes of a wave meet in a few bins
   uint32_t h2[2048], h3[1024];
-  uint32_t digit[3], above[3];
+  uint32_t digit[3], above[3], in_bin[3];
   uint32_t tot[4][2][kSelWaves];  // wave totals of the scans (three digits, one compaction)
   uint32_t c_gt[kSelThreads], c_eq[kSelThreads];
 };
@@ -291,14 +295,22 @@ __device__ __forceinline__ void topk_rows(const float* __restrict__ s, int L, in
         const bool hi = excl + c_hi >= kk;
         lds.digit[P] = hi ? bin_hi : bin_hi - 1;
         lds.above[P] = hi ? excl : excl + c_hi;
+        lds.in_bin[P] = hi ? c_hi : c_lo;
       }
       __syncthreads();
       kk -= __builtin_amdgcn_readfirstlane(lds.above[P]);
       return static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(lds.digit[P]));
     };
-    // digit 1 (bits 31 .. 21); "no key" counts in bin 0, below every key's bin
+    // digit 1 (bits 31 .. 21); "no key" counts in bin 0, below every key's bin.
+    // A wave of one bin (frames without sound, tokens without change) adds once:
+    // its lanes' adds to one address would follow one another.
     for_rounds(0, nr, [&](int, uint32_t key) __attribute__((always_inline)) {
-      atomicAdd(&lds.h1[((key >> 21) << 2) + (lane & 3)], 1u);
+      const uint32_t bin = key >> 21, f = __builtin_amdgcn_readfirstlane(bin);
+      if (__ballot(bin != f) == 0ull) {  // uniform
+        if (lane == 0) atomicAdd(&lds.h1[(f << 2) + (wave & 3)], static_cast<uint32_t>(kWave));
+      } else {
+        atomicAdd(&lds.h1[(bin << 2) + (lane & 3)], 1u);
+      }
     });
     __syncthreads();
     uint32_t c[2];
@@ -308,18 +320,34 @@ __device__ __forceinline__ void topk_rows(const float* __restrict__ s, int L, in
       c[j] = q.x + q.y + q.z + q.w;
     }
     uint32_t base = find(std::integral_constant<int, 0>{}, c[0], c[1], 2047u - 2u * tid) << 21;
-    // digits 2 (bits 20 .. 10) and 3 (bits 9 .. 0) of the keys in the bins before
-    for_rounds(0, nr, [&](int, uint32_t key) __attribute__((always_inline)) {
-      const uint32_t t = key - base;
-      if (t < (1u << 21)) atomicAdd(&lds.h2[t >> 10], 1u);
-    });
-    __syncthreads();
+    // digits 2 (bits 20 .. 10) and 3 (bits 9 .. 0) of the keys in the bin before.
+    // Where the bin is crowded (many keys tie), one lane adds for all of the wave's
+    // keys that meet the first one's bin.
+    const uint32_t crowd = static_cast<uint32_t>(L) / 8 + 256;
+    auto count = [&](uint32_t* h, uint32_t span, int shift, uint32_t keys_in) __attribute__((always_inline)) {
+      if (keys_in <= crowd) {
+        for_rounds(0, nr, [&](int, uint32_t key) __attribute__((always_inline)) {
+          const uint32_t t = key - base;
+          if (t < span) atomicAdd(&h[t >> shift], 1u);
+        });
+      } else {
+        for_rounds(0, nr, [&](int, uint32_t key) __attribute__((always_inline)) {
+          const uint32_t t = key - base;
+          const uint64_t in = __ballot(t < span);
+          if (in != 0ull) {  // uniform
+            const int lead = __builtin_ctzll(in);
+            const uint32_t bin = t >> shift, f = __builtin_amdgcn_readlane(bin, lead);
+            const uint64_t same = __ballot(t < span && bin == f);
+            if (t < span && (bin != f || lane == lead))
+              atomicAdd(&h[bin], bin == f ? static_cast<uint32_t>(__popcll(same)) : 1u);
+          }
+        });
+      }
+      __syncthreads();
+    };
+    count(lds.h2, 1u << 21, 10, __builtin_amdgcn_readfirstlane(lds.in_bin[0]));
     base += find(std::integral_constant<int, 1>{}, lds.h2[2047 - 2 * tid], lds.h2[2046 - 2 * tid], 2047u - 2u * tid) << 10;
-    for_rounds(0, nr, [&](int, uint32_t key) __attribute__((always_inline)) {
-      const uint32_t t = key - base;
-      if (t < (1u << 10)) atomicAdd(&lds.h3[t], 1u);
-    });
-    __syncthreads();
+    count(lds.h3, 1u << 10, 0, __builtin_amdgcn_readfirstlane(lds.in_bin[1]));
     base += find(std::integral_constant<int, 2>{}, lds.h3[1023 - tid], 0u, 1023u - tid);
     thr = base;
     need_eq = kk;
@@ -621,15 +649,18 @@ hipError_t launch_saliency(int dtype_bf16, const void* x, const void* xref, cons
 hipError_t launch_topk(const float* s, int L, int k, int threshold_mode, float threshold, int32_t* idx,
                        uint8_t* mask, int32_t* n_sel, hipStream_t stream, const double* num,
                        const double* den, double xi, double* step_delta) {
-  // four rounds of stores per workgroup, up to one workgroup per XCD
+  // two rounds of stores per workgroup or more, up to one workgroup per XCD; up to
+  // four rounds one workgroup does as well alone
   const int rounds = (L + kSelThreads - 1) / kSelThreads;
-  const int parts = rounds < 8 ? 1 : rounds / 4 < 8 ? rounds / 4 : 8;
+  const int parts = rounds < 5 ? 1 : rounds / 2 < 8 ? rounds / 2 : 8;
   const dim3 grid(parts + (step_delta != nullptr ? 1 : 0));
 #define ECHO_SEL_CASE(RK)                                                                      \
   if (L <= RK * kSelThreads)                                                                   \
     return ECHO_LAUNCH("select_rows", select_rows<RK>, grid, dim3(kSelThreads), 0, stream, s, L, \
                        k, threshold_mode, threshold, idx, mask, n_sel, num, den, sal_parts(L), xi, step_delta, parts);
   ECHO_SEL_CASE(1)
+  ECHO_SEL_CASE(2)
+  ECHO_SEL_CASE(4)
   ECHO_SEL_CASE(8)
   ECHO_SEL_CASE(32)
   ECHO_SEL_CASE(80)

@@ -50,15 +50,20 @@ def _hard_saliency(L, kind, seed):
         return s.astype(np.float32)
     if kind == "equal":
         return np.full(L, 0.25, np.float32)
+    if kind == "tied":      # silent frames, then ties beside a spread in the same digit
+        s = np.abs(rng.standard_normal(L)).astype(np.float32)
+        s[: L // 3] = 0.0
+        s[L // 3::2] = 0.7
+        return s
     bits = np.float32(0.75).view(np.uint32) + rng.integers(0, 4096, L).astype(np.uint32)
     return bits.astype(np.uint32).view(np.float32)
 
 
-@pytest.mark.parametrize("kind", ["special", "equal", "low_bits"])
-@pytest.mark.parametrize("L", [1, 1023, 1025, 7168, 8193, 32768, 32769, 81920, 81921])
+@pytest.mark.parametrize("kind", ["special", "equal", "tied", "low_bits"])
+@pytest.mark.parametrize("L", [1, 1023, 1025, 2049, 4096, 4097, 7168, 8193, 32768, 32769, 81920, 81921])
 def test_topk_edges(L, kind):
     """Sizes at the edges of the register forms and of the shared stores (from
-    8 rounds of 1024 keys), against a sort by (NaN first, value, index); exact."""
+    5 rounds of 1024 keys) and crowded digits, against a sort by (NaN first, value, index); exact."""
     s = _hard_saliency(L, kind, L)
     order = np.lexsort((np.arange(L), -np.where(np.isnan(s), 0.0, s.astype(np.float64)), ~np.isnan(s)))
     S = up(s)
