@@ -167,7 +167,12 @@ struct ChainLds {
 };
 
 // Workgroups [0, chains): one chain each.  Thread t of the W waves owns
-// elements 4 t + 256 W u (u < U) of a row; D <= 256 W U, D % 4 == 0.  Four
+// elements 4 t + 256 W u (u < U) of a row; D <= 256 W U, D % 4 == 0.  One wave
+// up to D = 768: little stream runs beside such chains, and the exchange between
+// waves is much of a token's time.  7080 tokens, 5898 rewritten, chains of 59 (us
+// a call: two launches / four waves / one wave): D = 296 80 / 86 / 73, D = 768
+// 82 / 95 / 84; at D = 1016 one wave of four pieces took 100 where the two
+// launches took 92.  Four
 // waves up to D = 5120: every wave of a chain repeats the decision and the
 // reductions, so five, eight and ten waves with fewer elements each were 5 to
 // 15% slower.  The next token's row of y_sel is loaded while the current one is
@@ -341,18 +346,24 @@ refcache_update(const T* __restrict__ x, const int32_t* __restrict__ idx, const 
     s.dot = wave_sum(s.dot);
     s.yy = wave_sum(s.yy);
     s.amax = wave_max(s.amax);
-    if (lane == 0) {
-      lds.d[slot][0][wave] = s.dot;
-      lds.d[slot][1][wave] = s.yy;
-      lds.d[slot][2][wave] = s.rr;
-      lds.f[slot][wave] = s.amax;
+    if constexpr (W == 1) {
+      __syncthreads();  // the token before's slot is known
+      if (made) store_ref(slot ^ 1);
+      if (fresh) rr = s.rr;
+    } else {
+      if (lane == 0) {
+        lds.d[slot][0][wave] = s.dot;
+        lds.d[slot][1][wave] = s.yy;
+        lds.d[slot][2][wave] = s.rr;
+        lds.f[slot][wave] = s.amax;
+      }
+      __syncthreads();
+      if (made) store_ref(slot ^ 1);
+      s.dot = row_sum(lds.d[slot][0][lane % 16]);
+      s.yy = row_sum(lds.d[slot][1][lane % 16]);
+      s.amax = row_max(lds.f[slot][lane % 16]);
+      if (fresh) rr = row_sum(lds.d[slot][2][lane % 16]);
     }
-    __syncthreads();
-    if (made) store_ref(slot ^ 1);
-    s.dot = row_sum(lds.d[slot][0][lane % 16]);
-    s.yy = row_sum(lds.d[slot][1][lane % 16]);
-    s.amax = row_max(lds.f[slot][lane % 16]);
-    if (fresh) rr = row_sum(lds.d[slot][2][lane % 16]);
     bool residual = false;
     if (have) {
       residual = similar(s.dot, s.yy, rr, tau);
@@ -460,6 +471,9 @@ static hipError_t refcache_update_t(const T* x, const int32_t* idx, const uint8_
 #define ECHO_RC_CASE(W, U)                         \
   if (D == 256 * W * U) ECHO_RC_LAUNCH(W, U, true) \
   if (D <= 256 * W * U) ECHO_RC_LAUNCH(W, U, false)
+  ECHO_RC_CASE(1, 1)
+  ECHO_RC_CASE(1, 2)
+  ECHO_RC_CASE(1, 3)
   ECHO_RC_CASE(4, 1)
   ECHO_RC_CASE(4, 2)
   ECHO_RC_CASE(4, 4)

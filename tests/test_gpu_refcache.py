@@ -94,7 +94,7 @@ def test_refcache_full_size():
     _run(L=32760, D=5120, chain_len=52, tau=0.5, dtype="bf16", steps=2, seed=6)
 
 
-@pytest.mark.parametrize("D,dtype", [(1024, "f32"), (3080, "bf16"), (5120, "f32"), (8184, "bf16"), (16384, "bf16")])
+@pytest.mark.parametrize("D,dtype", [(256, "bf16"), (296, "bf16"), (512, "f32"), (520, "bf16"), (1016, "bf16"), (1024, "f32"), (3080, "bf16"), (5120, "f32"), (8184, "bf16"), (16384, "bf16")])
 def test_refcache_row_widths(D, dtype):
     # every register width of the update kernel, full and one chunk short of it
     _run(L=48, D=D, chain_len=6, tau=0.4, dtype=dtype, steps=3, seed=7)
