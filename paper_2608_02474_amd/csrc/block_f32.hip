@@ -191,7 +191,10 @@ attn_fwd_f32(const float* __restrict__ q, int64_t ldq, const float* __restrict__
     const auto b = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
     return op(__uint_as_float(b[0]), __uint_as_float(b[1]));
   };
-  float m = -INFINITY, l = 0.0f;
+  // the running maximum starts at the lowest finite value: a wave without keys,
+  // or with none but -inf scores, merges with weight 0, and a NaN score reaches
+  // the result through the sums of the wave that has it
+  float m = -3.402823466e38f, l = 0.0f;
   int key0 = 16 * wave;
   if (key0 < L) fetch(key0, kn, vn);
   for (; key0 < L; key0 += 16 * F32_WAVES) {
@@ -217,7 +220,7 @@ attn_fwd_f32(const float* __restrict__ q, int64_t ldq, const float* __restrict__
       mx = fmaxf(mx, sc[r]);
     }
     mx = across(mx, [](float a, float b) { return fmaxf(a, b); });
-    const float m_new = fmaxf(m, mx);  // a group has a key below L
+    const float m_new = fmaxf(m, mx);
     const float alpha = expf(m - m_new);
     float pv[4], ps = 0.0f;
 #pragma unroll
@@ -257,7 +260,7 @@ attn_fwd_f32(const float* __restrict__ q, int64_t ldq, const float* __restrict__
     float lt = 0.0f, ot = 0.0f;
 #pragma unroll
     for (int w = 0; w < F32_WAVES; ++w) {
-      const float f = sl[w][qi] > 0.0f ? expf(sm[w][qi] - mt) : 0.0f;  // a wave without keys adds nothing
+      const float f = expf(sm[w][qi] - mt);
       lt += f * sl[w][qi];
       ot += f * so[w][d][qi];
     }

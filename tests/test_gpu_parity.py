@@ -385,6 +385,49 @@ def test_block_partial_f32_edges(w):
         assert torch.equal(ys, full[torch.from_numpy(idx.astype(np.int64)).to(full.device)]), n
 
 
+
+# attention forms with their waves' partial results merged at the end, one whose waves do not share keys, and
+# waves without keys
+NON_FINITE = [
+    synth.Workload("nan_f32_40tok", T=2, grid=(4, 5), D=64, H=2, F=72, n_samples=4000, ratio=0.5, dtype="f32",
+                   audio="speech", seed=91),
+    synth.Workload("nan_f32_130tok", T=2, grid=(5, 13), D=256, H=2, F=256, n_samples=4000, ratio=0.5, dtype="f32",
+                   audio="speech", seed=92),
+    synth.Workload("nan_bf16_300tok", T=3, grid=(10, 10), D=256, H=2, F=512, n_samples=4000, ratio=0.5,
+                   dtype="bf16", audio="speech", seed=93),
+]
+
+
+@pytest.mark.parametrize("w", NON_FINITE, ids=lambda w: w.name)
+def test_block_partial_nan_token_reaches_every_row(w):
+    """A token whose latent is NaN has a NaN key, which every query's softmax
+    contains: no row may come out finite, wherever the token lies."""
+    p = synth.make_block_weights(w)
+    _, x = synth.make_latents(w)
+    for at in (0, 5, 17, w.L - 1):
+        bad = x.copy()
+        bad[at] = np.nan
+        say(f"nan {w.name} token {at}")
+        assert np.isnan(_block_gpu(w, p, bad, np.arange(w.L))).all(), at
+
+
+def test_block_partial_f32_scores_of_minus_infinity():
+    """Scores below the fp32 range (-inf) have weight 0, whole groups of them
+    too: head 0 sees one finite score, at token 20, and takes that token's value."""
+    w = NON_FINITE[0]
+    p = synth.make_block_weights(w)
+    dh = w.D // w.H
+    for n in ("wq", "bq", "wk", "bk"):
+        p[n][:dh] = 0.0
+    p["bq"][0], p["wk"][0, 0], p["bk"][0] = 1e19, 1e20, -1e20
+    p["mod"][:2] = 0.0
+    sign = -np.ones(w.L, np.float32)
+    sign[20] = 1.0
+    # rows of +-1, which the LayerNorm keeps: key element 0 is about 0 for token 20 and -2e20 for the others
+    x = sign[:, None] * np.where(np.arange(w.D) % 2 == 0, 1.0, -1.0).astype(np.float32)
+    check_block(_block_gpu(w, p, x, np.arange(w.L)), OB.block_partial(p, x, np.arange(w.L), w.H), w.dtype, "-inf scores")
+
+
 # shapes whose attention runs items of 128 and of 256 queries (its other kernels run in the blocks above)
 ITEMS = [
     synth.Workload("items128_bf16_400tok", T=4, grid=(10, 10), D=2560, H=20, F=512, n_samples=4000, ratio=0.5,
