@@ -199,7 +199,8 @@ __device__ __forceinline__ void topk_rows(const float* __restrict__ s, int L, in
   uint32_t kr[RR];
   // The thread's index through an empty asm for each pass, and a barrier to
   // the scheduler after each round: the indexes, addresses and bounds of up to
-  // 80 rounds, computed once and kept from pass to pass, would spill.
+  // 80 rounds, computed once and kept from pass to pass, would spill (64 rounds
+  // spill 8 registers so, 80 rounds 87).
   auto fresh_tid = [&]() __attribute__((always_inline)) {
     int t = tid;
     asm volatile("" : "+v"(t));
@@ -220,7 +221,8 @@ __device__ __forceinline__ void topk_rows(const float* __restrict__ s, int L, in
       __builtin_amdgcn_sched_barrier(0);
     }
   }
-  const int nr = R > 0 ? R : (L + kSelThreads - 1) / kSelThreads;
+  const int rounds = (L + kSelThreads - 1) / kSelThreads;
+  const int nr = R > 0 ? R : rounds;  // the passes over registers are unrolled whole
   // body(r, key) for the rounds r0 .. r1 - 1
   auto for_rounds = [&](int r0, int r1, auto&& body) __attribute__((always_inline)) {
     if constexpr (R > 0) {
@@ -391,8 +393,7 @@ __device__ __forceinline__ void topk_rows(const float* __restrict__ s, int L, in
     // (the comparisons of a. done again, not their 64-bit results kept: two per
     // round would spill)
     asm volatile("" : "+s"(thr));
-    const int w0 = static_cast<int>(static_cast<int64_t>(nr) * part / parts);
-    const int w1 = static_cast<int>(static_cast<int64_t>(nr) * (part + 1) / parts);
+    const int w0 = rounds * part / parts, w1 = rounds * (part + 1) / parts;  // of the rounds that hold keys
     const int tc = fresh_tid();
     const uint32_t my_rank = lds.c_eq[lane * kSelWaves + wave], my_first = lds.c_gt[lane * kSelWaves + wave];
     for_rounds(r0 > w0 ? r0 : w0, r1 < w1 ? r1 : w1, [&](int r, uint32_t key) __attribute__((always_inline)) {
@@ -653,6 +654,11 @@ hipError_t launch_topk(const float* s, int L, int k, int threshold_mode, float t
   // four rounds one workgroup does as well alone
   const int rounds = (L + kSelThreads - 1) / kSelThreads;
   const int parts = rounds < 5 ? 1 : rounds / 2 < 8 ? rounds / 2 : 8;
+  // A form of R rounds walks R rounds in every pass, so the forms lie close
+  // together: 9000 keys took 18.8 us in the form of 32 rounds and take 13.0 in that of
+  // 16, 16384 keys 19.0 and 13.3, 33000 keys 55.8 (80 rounds) and 25.4 (48), 60000
+  // keys 56.2 (80) and 32.5 (64).  (Passes bounded by the rounds at run time: 16.6,
+  // 18.2, 44, 50, and 2 us more where the form is full.)
   const dim3 grid(parts + (step_delta != nullptr ? 1 : 0));
 #define ECHO_SEL_CASE(RK)                                                                      \
   if (L <= RK * kSelThreads)                                                                   \
@@ -662,7 +668,10 @@ hipError_t launch_topk(const float* s, int L, int k, int threshold_mode, float t
   ECHO_SEL_CASE(2)
   ECHO_SEL_CASE(4)
   ECHO_SEL_CASE(8)
+  ECHO_SEL_CASE(16)
   ECHO_SEL_CASE(32)
+  ECHO_SEL_CASE(48)
+  ECHO_SEL_CASE(64)
   ECHO_SEL_CASE(80)
 #undef ECHO_SEL_CASE
   return ECHO_LAUNCH("select_rows", select_rows<0>, grid, dim3(kSelThreads), 0, stream, s, L, k,

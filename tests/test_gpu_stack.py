@@ -60,7 +60,8 @@ def _hard_saliency(L, kind, seed):
 
 
 @pytest.mark.parametrize("kind", ["special", "equal", "tied", "low_bits"])
-@pytest.mark.parametrize("L", [1, 1023, 1025, 2049, 4096, 4097, 7168, 8193, 32768, 32769, 81920, 81921])
+@pytest.mark.parametrize("L", [1, 1023, 1025, 2049, 4096, 4097, 7168, 8193, 16384, 16385, 32768, 32769,
+                               49152, 49153, 65536, 65537, 81920, 81921])
 def test_topk_edges(L, kind):
     """Sizes at the edges of the register forms and of the shared stores (from
     5 rounds of 1024 keys) and crowded digits, against a sort by (NaN first, value, index); exact."""
