@@ -169,7 +169,7 @@ __device__ __forceinline__ uint32_t lanes_below(uint64_t mask) {
 
 // LDS of one selection
 struct TopkLds {
-  uint32_t h1[2048 * 4];  // digit 1, four copies side by side (a lane uses copy lane % 4): the keys of a
+  alignas(16) uint32_t h1[2048 * 4];  // digit 1, four copies side by side (a lane uses copy lane % 4): the keys of a
                           // step lie in a few octaves, so that most lanes of a wave meet in a few bins
   uint32_t h2[2048], h3[1024];
   uint32_t digit[3], above[3], in_bin[3];
