@@ -15,12 +15,14 @@
 //                     current reference row in registers; fp64 similarity, int8
 //                     residual or new reference (pops only; a chain's old
 //                     reference that only the chain still held is reused in
-//                     place), the fresh output cast(y_sel) and the saliency
-//                     reference := x.  The rest rebuild the other rows from
-//                     their entries, one wave per row.
+//                     place).  The rest rebuild the other rows from their
+//                     entries, one wave per row.  The fresh output cast(y_sel)
+//                     and the saliency reference := x of the rewritten rows are
+//                     written by the chains or by further waves (see the rule
+//                     at the launch).
 // The two parts of refcache_update touch different rows: a token that is not
 // rewritten holds its reference, so no chain writes that slot.  A chain is
-// bound by latency (its tokens one after another), the rebuilt rows by HBM, so
+// bound by latency (its tokens one after another), the other rows by HBM, so
 // run together the scan hides behind the stream, and y_sel is read once
 // instead of twice (32760 x 5120 bf16, chains of 52, 13104 rewritten: scan
 // 123 us, then a fusion pass of 183 us -> 217 us together, 5.7 TB/s of what has
@@ -168,20 +170,19 @@ struct ChainLds {
 
 // Workgroups [0, chains): one chain each.  Thread t of the W waves owns
 // elements 4 t + 256 W u (u < U) of a row; D <= 256 W U, D % 4 == 0.  One wave
-// up to D = 768: little stream runs beside such chains, and the exchange between
-// waves is much of a token's time.  7080 tokens, 5898 rewritten, chains of 59 (us
-// a call: two launches / four waves / one wave): D = 296 80 / 86 / 73, D = 768
-// 82 / 95 / 84; at D = 1016 one wave of four pieces took 100 where the two
-// launches took 92.  Four
+// up to D = 768, where the exchange between waves is much of a token's time, four
 // waves up to D = 5120: every wave of a chain repeats the decision and the
 // reductions, so five, eight and ten waves with fewer elements each were 5 to
-// 15% slower.  The next token's row of y_sel is loaded while the current one is
+// 15% slower there, and two waves at D = 520 to 1024 2 to 21% slower than these
+// forms with STREAM.  The next token's row of y_sel is loaded while the current one is
 // processed, and a token's stores are issued after that load, whose wait would
 // otherwise include them.  Taking a slot from the free stack is two dependent
 // memory operations of one wave: a new reference's row is stored after the
 // next token's barrier, when the slot is known, and until then stays in
 // registers.
-// Workgroups from `chains` on: one wave per row i, rebuilt from its entry if
+// Workgroups from `chains` on: STREAM: one wave per rewritten row first, which
+// writes its y and xref, so that a chain's tokens carry no more than they have
+// to.  Then one wave per row i, rebuilt from its entry if
 // mask[i] == 0; up to 5 of a lane's chunks of 8 elements are loaded before any
 // is used.  They run in the waves that the chains leave free, so the registers
 // decide how much of the stream runs beside the scan: full bf16 rows of 5120
@@ -189,7 +190,7 @@ struct ChainLds {
 // Streams that nothing reads again before the next step are non-temporal
 // (y_sel, x, y, xref, codes); the reference rows, shared by the tokens of a
 // chain, keep ordinary accesses.
-template <typename T, int W, int U, bool FULL>
+template <typename T, int W, int U, bool FULL, bool STREAM>
 __global__ void __launch_bounds__(W * kWave, sizeof(T) == 2 && U == 5 && FULL ? 4 : 1)
 refcache_update(const T* __restrict__ x, const int32_t* __restrict__ idx, const uint8_t* __restrict__ mask,
                 int n_sel, int L, int D, int chains, int chain_len, float tau,
@@ -203,9 +204,37 @@ refcache_update(const T* __restrict__ x, const int32_t* __restrict__ idx, const 
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave), lane = tid % kWave;
 
   if (static_cast<int>(blockIdx.x) >= chains) {
-    const int64_t i = static_cast<int64_t>(blockIdx.x - chains) * W + wave;
-    if (i >= L || mask[i]) return;
+    int64_t i = static_cast<int64_t>(blockIdx.x - chains) * W + wave;
     const int nch = D / 8;
+    if constexpr (STREAM) {
+      if (i < n_sel) {
+        const int64_t row = static_cast<int64_t>(idx[i]) * D;
+        const float* ys = y_sel + i * D;
+        constexpr int B = (W * U + 1) / 2;  // chunks per lane: the whole row at once
+        Raw8<float> yr[B];
+        Raw8<T> xr[B];
+#pragma unroll
+        for (int u = 0; u < B; ++u) {
+          const int c = lane + u * kWave;
+          if (c >= nch) continue;
+          yr[u].load(ys + c * 8);
+          xr[u].load_nt(x + row + c * 8);
+        }
+#pragma unroll
+        for (int u = 0; u < B; ++u) {
+          const int c = lane + u * kWave;
+          if (c >= nch) continue;
+          float v[8];
+          yr[u].unpack(v);
+          stg16_nt(y_out + row + c * 8, pack16(v, static_cast<const T*>(nullptr)));
+          if (sizeof(T) == 4) stg16_nt(y_out + row + c * 8 + 4, pack16(v + 4, static_cast<const T*>(nullptr)));
+          xr[u].store(xref + row + c * 8);
+        }
+        return;
+      }
+      i -= n_sel;
+    }
+    if (i >= L || mask[i]) return;
     const int kind = ent_kind[i];
     const T* rp = pool + static_cast<int64_t>(ent_slot[i] < 0 ? 0 : ent_slot[i]) * D;
     const float sc = scale[i];
@@ -341,8 +370,10 @@ refcache_update(const T* __restrict__ x, const int32_t* __restrict__ idx, const 
     }
     // x only passes through: loaded here, after the sums, its registers are
     // the sums' (loaded a token ahead like y_sel: 238 -> 227 us without)
+    if constexpr (!STREAM) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) xr[u].load_nt(x + row + at(u));
+      for (int u = 0; u < U; ++u) xr[u].load_nt(x + row + at(u));
+    }
     s.dot = wave_sum(s.dot);
     s.yy = wave_sum(s.yy);
     s.amax = wave_max(s.amax);
@@ -386,8 +417,9 @@ refcache_update(const T* __restrict__ x, const int32_t* __restrict__ idx, const 
             if (have) refcount[cr] = held - 1;
           } else {
             // cannot happen with capacity >= L + chains; kept so that a broken
-            // invariant leaves the token without an entry instead of writing
-            // outside the pool
+            // invariant leaves the token without an entry, and its chain with
+            // nothing to compare with for the rest of the call, instead of
+            // writing outside the pool
             atomicAdd(free_top, 1);
             ns = -1;
           }
@@ -403,13 +435,15 @@ refcache_update(const T* __restrict__ x, const int32_t* __restrict__ idx, const 
         lds.ref[slot] = ns;
       }
     }
+    if constexpr (!STREAM) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      if (!in(u)) continue;
-      Raw4<T> o;
-      o.pack(y[u]);
-      o.store_nt(y_out + row + col(u));
-      xr[u].store_nt(xref + row + col(u));
+      for (int u = 0; u < U; ++u) {
+        if (!in(u)) continue;
+        Raw4<T> o;
+        o.pack(y[u]);
+        o.store_nt(y_out + row + col(u));
+        xr[u].store_nt(xref + row + col(u));
+      }
     }
     if (residual) {
       const float inv = s.amax > 0.0f ? __fdiv_rn(127.0f, s.amax) : 0.0f;
@@ -459,29 +493,44 @@ static hipError_t refcache_update_t(const T* x, const int32_t* idx, const uint8_
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
+  // The rewritten rows' y and xref by waves of their own, which read y_sel a
+  // second time, while the rows are few enough for that read to hit the caches
+  // (256 MB behind HBM; a call moves up to six times its rows) and the chains
+  // narrow enough that the scan is what the call waits for.  Chains that write
+  // / waves that write, us a call: 7080 tokens, chains of 59, 83% rewritten, bf16
+  // D = 520 82 / 68, 640 83 / 70, 776 85 / 67, 1016 90 / 70, 1536 105 / 84, 2048 97
+  // / 79, fp32 D = 520 75 / 66, 1024 90 / 73 (a scan and then a fusion pass took 80,
+  // 82, 83, 86, 107, 112, 84, 95); 32760 tokens, all rewritten, bf16 D = 1024 128
+  // / 122, but D = 2048 169 / 185, fp32 D = 1024 140 / 150; 75600 tokens of D = 768
+  // bf16, 30% rewritten, 95 / 104.
+  const bool stream_rows = D <= 2048 && static_cast<int64_t>(L) * D * sizeof(T) <= (int64_t(1) << 26);
   // the chains first: they take longest and stay resident beside the stream
-#define ECHO_RC_LAUNCH(W, U, FULL)                                                                             \
-  {                                                                                                            \
-    const dim3 grid(static_cast<unsigned>(chains + (static_cast<int64_t>(L) + W - 1) / W));                    \
-    hipLaunchKernelGGL((refcache_update<T, W, U, FULL>), grid, dim3(W * kWave), 0, stream, x, idx, mask, n_sel, \
-                       L, D, chains, chain_len, tau, y_sel, pool, refcount, free_list, free_top, chain_ref,    \
-                       ent_slot, ent_kind, codes, scale, xref, y);                                             \
-    return hipGetLastError();                                                                                  \
+#define ECHO_RC_LAUNCH(W, U, FULL, STREAM)                                                                          \
+  {                                                                                                                 \
+    const int64_t rows = static_cast<int64_t>(L) + (STREAM ? n_sel : 0);                                            \
+    const dim3 grid(static_cast<unsigned>(chains + (rows + W - 1) / W));                                            \
+    hipLaunchKernelGGL((refcache_update<T, W, U, FULL, STREAM>), grid, dim3(W * kWave), 0, stream, x, idx, mask,   \
+                       n_sel, L, D, chains, chain_len, tau, y_sel, pool, refcount, free_list, free_top, chain_ref,  \
+                       ent_slot, ent_kind, codes, scale, xref, y);                                                  \
+    return hipGetLastError();                                                                                       \
   }
-#define ECHO_RC_CASE(W, U)                         \
-  if (D == 256 * W * U) ECHO_RC_LAUNCH(W, U, true) \
-  if (D <= 256 * W * U) ECHO_RC_LAUNCH(W, U, false)
-  ECHO_RC_CASE(1, 1)
-  ECHO_RC_CASE(1, 2)
-  ECHO_RC_CASE(1, 3)
-  ECHO_RC_CASE(4, 1)
-  ECHO_RC_CASE(4, 2)
-  ECHO_RC_CASE(4, 4)
-  ECHO_RC_CASE(4, 5)
-  ECHO_RC_CASE(8, 4)
-  ECHO_RC_CASE(16, 4)
+#define ECHO_RC_CASE(W, U, STREAM)                         \
+  if (D == 256 * W * U) ECHO_RC_LAUNCH(W, U, true, STREAM) \
+  if (D <= 256 * W * U) ECHO_RC_LAUNCH(W, U, false, STREAM)
+#define ECHO_RC_NARROW(STREAM)                                                              \
+  ECHO_RC_CASE(1, 1, STREAM) ECHO_RC_CASE(1, 2, STREAM) ECHO_RC_CASE(1, 3, STREAM)          \
+  ECHO_RC_CASE(4, 1, STREAM) ECHO_RC_CASE(4, 2, STREAM)
+  if (stream_rows) {
+    ECHO_RC_NARROW(true)
+  }
+  ECHO_RC_NARROW(false)
+  ECHO_RC_CASE(4, 4, false)
+  ECHO_RC_CASE(4, 5, false)
+  ECHO_RC_CASE(8, 4, false)
+  ECHO_RC_CASE(16, 4, false)
 #undef ECHO_RC_LAUNCH
 #undef ECHO_RC_CASE
+#undef ECHO_RC_NARROW
   return hipErrorInvalidValue;
 }
 

@@ -96,8 +96,27 @@ def test_refcache_full_size():
 
 @pytest.mark.parametrize("D,dtype", [(256, "bf16"), (296, "bf16"), (512, "f32"), (520, "bf16"), (1016, "bf16"), (1024, "f32"), (3080, "bf16"), (5120, "f32"), (8184, "bf16"), (16384, "bf16")])
 def test_refcache_row_widths(D, dtype):
-    # every register width of the update kernel, full and one chunk short of it
+    # a full row or a part of one in every register width of the update kernel
     _run(L=48, D=D, chain_len=6, tau=0.4, dtype=dtype, steps=3, seed=7)
+
+
+@pytest.mark.parametrize("D", [256, 512, 768, 1024, 2048, 4096, 5120, 8192, 16384])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_refcache_register_widths(D, dtype):
+    """Every register width of the update kernel, filled and one chunk of 8 short
+    of it, in both types."""
+    for d in (D, D - 8):
+        _run(L=36, D=d, chain_len=6, tau=0.4, dtype=dtype, steps=2, seed=10)
+
+
+@pytest.mark.parametrize("D,L,chain_len,dtype", [(512, 33000, 60, "f32"), (768, 43740, 54, "bf16"),
+                                                 (1016, 16600, 50, "f32"), (1024, 32800, 40, "bf16"),
+                                                 (2040, 16500, 60, "bf16"), (2048, 8240, 40, "f32")])
+def test_refcache_rows_past_the_caches(D, L, chain_len, dtype):
+    """Narrow rows of more than 64 MB, whose fresh outputs the chains write
+    (fewer go through waves of their own, as in the tests above)."""
+    assert L * D * (2 if dtype == "bf16" else 4) > 1 << 26
+    _run(L=L, D=D, chain_len=chain_len, tau=0.5, dtype=dtype, steps=2, seed=11)
 
 
 def test_refcache_nothing_rewritten():
