@@ -185,13 +185,15 @@ struct ChainLds {
 // to.  Then one wave per row i, rebuilt from its entry if
 // mask[i] == 0; up to 5 of a lane's chunks of 8 elements are loaded before any
 // is used.  They run in the waves that the chains leave free, so the registers
-// decide how much of the stream runs beside the scan: full bf16 rows of 5120
-// are held to 128 (four waves per SIMD, the chains of a 480p clip taking 2.5).
+// decide how much of the stream runs beside the scan: full bf16 rows, which
+// come to 128 and little more, are held to that, four waves per SIMD (D = 5120,
+// 32760 rows, 40% rewritten 238 -> 225 us, 83% 350 -> 354; 4096 and 8192 the same
+// either way).  Others would spill: D = 4608 bf16 319 -> 687 us, fp32 489 -> 508.
 // Streams that nothing reads again before the next step are non-temporal
 // (y_sel, x, y, xref, codes); the reference rows, shared by the tokens of a
 // chain, keep ordinary accesses.
 template <typename T, int W, int U, bool FULL, bool STREAM>
-__global__ void __launch_bounds__(W * kWave, sizeof(T) == 2 && U == 5 && FULL ? 4 : 1)
+__global__ void __launch_bounds__(W * kWave, sizeof(T) == 2 && FULL ? 4 : 1)
 refcache_update(const T* __restrict__ x, const int32_t* __restrict__ idx, const uint8_t* __restrict__ mask,
                 int n_sel, int L, int D, int chains, int chain_len, float tau,
                 const float* __restrict__ y_sel, T* __restrict__ pool, int32_t* __restrict__ refcount,
