@@ -1143,16 +1143,23 @@ size_t attn_partial_bytes(int Mq_max, int L, int H) {
   return sizeof(float) * static_cast<size_t>(G) * 2 * C::kQ * (ATT_DH + 2);
 }
 
+// timing names: one per form, so that a caller sees which one ran
+static const char* const kAttNames[2][5] = {
+    {"attn_fwd_bf16", "attn_fwd_bf16_q384", "attn_fwd_bf16_q256", "attn_fwd_bf16_q128", "attn_fwd_bf16_short"},
+    {"attn_cross_bf16", "attn_cross_bf16_q384", "attn_cross_bf16_q256", "attn_cross_bf16_q128",
+     "attn_cross_bf16_short"}};
+
 hipError_t launch_attn_bf16(const bf16_t* q, int64_t ldq, const bf16_t* k, const bf16_t* v,
                             int64_t ldkv, int Mq, int L, int H, bf16_t* out, int64_t ldo,
-                            float* part, size_t part_bytes, hipStream_t stream, const char* timing_name) {
+                            float* part, size_t part_bytes, hipStream_t stream, bool cross) {
   if (Mq <= 0) return hipSuccess;
   const float scale_log2 = static_cast<float>(1.4426950408889634 / sqrt(static_cast<double>(ATT_DH)));
   const int ncu = device_cu_count();
   AttPlan plan = att_plan<AttCfg<1, 12>::kQ>(Mq, L, H, ncu);
   if (part_bytes < plan.bytes) plan.balanced = false;
-  ::echo::TimedLaunch scope(timing_name, stream);
-  switch (att_choose(plan, part != nullptr, Mq, L, H, ncu)) {
+  const AttKind kind = att_choose(plan, part != nullptr, Mq, L, H, ncu);
+  ::echo::TimedLaunch scope(kAttNames[cross][kind], stream);
+  switch (kind) {
     case ATT_BALANCED:
       return launch_attn_balanced(plan, q, ldq, k, v, ldkv, Mq, L, H, scale_log2, out, ldo, part, stream);
     case ATT_256:

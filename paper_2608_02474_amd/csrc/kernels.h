@@ -142,7 +142,7 @@ hipError_t launch_gemm_f32_pair(const char* name, const GemmF32Args& a, const Ge
 hipError_t launch_attn_bf16(const bf16_t* q, int64_t ldq, const bf16_t* k, const bf16_t* v,
                             int64_t ldkv, int Mq, int L, int H, bf16_t* out, int64_t ldo,
                             float* part, size_t part_bytes, hipStream_t stream,
-                            const char* timing_name = "attn_fwd_bf16");
+                            bool cross = false);
 size_t attn_partial_bytes(int Mq_max, int L, int H);
 // bytes that hold the partial results of the GEMMs' split tails (256 fp32
 // tiles of 256 x 256)

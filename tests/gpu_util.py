@@ -52,6 +52,21 @@ def down(t: torch.Tensor) -> np.ndarray:
     return t.detach().float().cpu().numpy() if t.dtype == torch.bfloat16 else t.detach().cpu().numpy()
 
 
+def attention_forms(run):
+    """run(), and the attention kernels it launched (their timing names: the
+    balanced key ranges have none of the suffixes _q384, _q256, _q128 for whole
+    items of that many queries and _short)."""
+    from paper_2608_02474_amd import api
+    api.profile_enable(True)
+    try:
+        api.profile_read()
+        out = run()
+        names = {n for n in api.profile_read() if n.startswith("attn_")}
+    finally:
+        api.profile_enable(False)
+    return out, names
+
+
 def check_block(got: np.ndarray, want: np.ndarray, dtype: str, what: str = "y_sel"):
     got = np.asarray(got, np.float64)
     want = np.asarray(want, np.float64)

@@ -14,8 +14,8 @@ from oracle import select as OS
 from oracle import step as OST
 from paper_2608_02474_amd import api
 
-from gpu_util import (check_block, check_selection, device, down, params_to_device, say, tdtype,
-                      up, TOL_BF16_ABS, TOL_BF16_REL_L2, TOL_F32_ABS)
+from gpu_util import (attention_forms, check_block, check_selection, device, down, params_to_device, say,
+                      tdtype, up, TOL_BF16_ABS, TOL_BF16_REL_L2, TOL_F32_ABS)
 
 pytestmark = pytest.mark.gpu
 
@@ -231,10 +231,13 @@ def test_cache_update_empty_and_full():
 
 # -------------------------------------------------------------------- block
 
-def _block_gpu(w, p, x, idx):
+def _block_gpu(w, p, x, idx, form=None, batch_invariant=False):
+    """The block's rows; form: the attention kernel that has to have run."""
     P = params_to_device(p, w.dtype)
-    ys = api.block_partial(P, up(x, tdtype(w.dtype)), up(np.asarray(idx, np.int32)), len(idx), w.H)
+    X, I = up(x, tdtype(w.dtype)), up(np.asarray(idx, np.int32))
+    ys, forms = attention_forms(lambda: api.block_partial(P, X, I, len(idx), w.H, batch_invariant=batch_invariant))
     torch.cuda.synchronize()
+    assert form is None or forms == {form}, forms
     return down(ys)
 
 
@@ -276,9 +279,10 @@ def test_block_partial_ln2_widths(w):
         check_block(got, want, w.dtype, f"{w.name}/{name}")
 
 
-# bf16 shapes at the edges of the attention tiling: one ragged key tile, exactly
-# one tile, one tile plus one key, three tiles, and query sets that cross a
-# 384-query workgroup (with the key-split tail of a few items)
+# bf16 shapes at the edges of the attention's 64-key tiles and 32-key blocks: one
+# ragged tile, exactly one tile, one tile plus one key, three tiles, and query
+# sets that cross a 384-query workgroup.  So few queries and keys go to the
+# short kernel; batch-invariant blocks take whole items of 384 queries at any size
 EDGE = [synth.Workload(f"edge_bf16_{T * gh * gw}tok", T=T, grid=(gh, gw), D=256, H=2, F=512,
                        n_samples=4000, ratio=0.5, dtype="bf16", audio="bursts", seed=30 + T * gh * gw)
         for T, gh, gw in [(2, 4, 5), (1, 8, 8), (5, 1, 13), (2, 5, 13), (4, 10, 12)]]
@@ -293,20 +297,36 @@ def test_block_partial_attention_edges(w):
     for name, idx in {"half": np.sort(rng.choice(w.L, w.L // 2, replace=False)),
                       "one": np.array([0]), "all": np.arange(w.L)}.items():
         say(f"block {w.name} {name} n={len(idx)}")
-        got = _block_gpu(w, p, x, idx)
+        got = _block_gpu(w, p, x, idx, form="attn_fwd_bf16_short")
         want = OB.block_partial(p, x, idx, w.H, kv=kv)
         check_block(got, want, w.dtype, f"{w.name}/{name}")
 
 
-# bf16 shapes whose attention runs the balanced key ranges (at least 32 key
-# tiles): few items, so that every item is cut into many pieces merged by the
-# combine; query counts that leave the last query tile of a head with 48, 160
-# and 288 queries (one, two and three waves with queries on the busiest
-# SIMD: the three costs of a short item), whole tiles only, and every token;
-# the 2100-token shape ends in a ragged key tile
+@pytest.mark.parametrize("w", EDGE + [RAGGED], ids=lambda w: w.name)
+def test_block_partial_attention_edges_whole_items(w):
+    """The same edges in the kernel of 384-query items, against the oracle."""
+    p = synth.make_block_weights(w)
+    _, x = synth.make_latents(w)
+    rng = np.random.default_rng(11)
+    kv = OB.kv_projection(OB._f64(p), np.asarray(x, np.float64))
+    for name, idx in {"half": np.sort(rng.choice(w.L, w.L // 2, replace=False)),
+                      "one": np.array([0]), "all": np.arange(w.L)}.items():
+        say(f"block {w.name} {name} n={len(idx)}")
+        got = _block_gpu(w, p, x, idx, form="attn_fwd_bf16_q384", batch_invariant=True)
+        check_block(got, OB.block_partial(p, x, idx, w.H, kv=kv), w.dtype, f"{w.name}/{name}")
+
+
+# bf16 shapes with enough key tiles (32) for the balanced key ranges: few items,
+# so that every item is cut into many pieces merged by the combine; query
+# counts that leave the last query tile of a head with 48, 160 and 288 queries
+# (one, two and three waves with queries on the busiest SIMD: the three costs
+# of a short item), whole tiles only, and every token.  The 2600-token shape
+# runs the ranges at every count and ends in a ragged key tile; the 2560-token
+# one at all but every token, the 2100-token one at 48 (the short kernel
+# otherwise)
 BALANCED = [synth.Workload(f"balanced_bf16_{T * gh * gw}tok", T=T, grid=(gh, gw), D=256, H=2, F=512,
                            n_samples=8000, ratio=0.3, dtype="bf16", audio="speech", seed=70 + T)
-            for T, gh, gw in [(5, 16, 32), (3, 20, 35)]]
+            for T, gh, gw in [(5, 16, 32), (3, 20, 35), (5, 20, 26)]]
 
 
 @pytest.mark.parametrize("w", BALANCED, ids=lambda w: w.name)
@@ -318,7 +338,8 @@ def test_block_partial_balanced_ranges(w):
     for n in (48, 432, 544, 672, 768, w.L):
         idx = np.sort(rng.choice(w.L, n, replace=False))
         say(f"block {w.name} n={n}")
-        got = _block_gpu(w, p, x, idx)
+        ranges = w.L == 2600 or (w.L == 2560 and n < w.L) or n == 48
+        got = _block_gpu(w, p, x, idx, form="attn_fwd_bf16" if ranges else "attn_fwd_bf16_short")
         want = OB.block_partial(p, x, idx, w.H, kv=kv)
         check_block(got, want, w.dtype, f"{w.name}/n={n}")
 
@@ -447,7 +468,7 @@ def test_block_partial_attention_items(w):
         idx = np.sort(rng.choice(w.L, n, replace=False))
         rows = np.unique(np.r_[0, n - 1, np.arange(0, n, 29), n - n % 128 - 1])
         say(f"block {w.name} n={n}")
-        got = _block_gpu(w, p, x, idx)[rows]
+        got = _block_gpu(w, p, x, idx, form=f"attn_fwd_bf16_q{128 if w is ITEMS[0] else 256}")[rows]
         check_block(got, OB.block_partial(p, x, idx[rows], w.H, kv=kv), w.dtype, f"{w.name}/n={n}")
 
 
@@ -463,7 +484,8 @@ def test_block_partial_attention_rescale_few_keys():
     _, x = synth.make_latents(w)
     kv = OB.kv_projection(OB._f64(p), np.asarray(x, np.float64))
     idx = np.sort(np.random.default_rng(15).choice(w.L, 200, replace=False))
-    check_block(_block_gpu(w, p, x, idx), OB.block_partial(p, x, idx, w.H, kv=kv), w.dtype, "rescale, few keys")
+    got = _block_gpu(w, p, x, idx, form="attn_fwd_bf16_short")
+    check_block(got, OB.block_partial(p, x, idx, w.H, kv=kv), w.dtype, "rescale, few keys")
 
 
 def _reference_moves(q, k, H):
@@ -505,9 +527,29 @@ def test_block_partial_attention_rescale():
     moves = _reference_moves(q, kv[1], w.H)
     say(f"rescale: rows whose reference moves {np.mean(moves > 0):.2f}, moves per row up to {moves.max()}")
     assert np.mean(moves > 0) > 0.5 and np.mean(moves == 0) > 0.01
-    got = _block_gpu(w, p, x, idx)
     want = OB.block_partial(p, x, idx, w.H, kv=kv)
-    check_block(got, want, w.dtype, "rescale")
+    check_block(_block_gpu(w, p, x, idx, form="attn_fwd_bf16"), want, w.dtype, "rescale")
+    got = _block_gpu(w, p, x, idx, form="attn_fwd_bf16_q384", batch_invariant=True)
+    check_block(got, want, w.dtype, "rescale, whole items")
+
+
+@pytest.mark.parametrize("w", ITEMS, ids=lambda w: w.name)
+def test_block_partial_attention_rescale_items(w):
+    """The same peaked scores (std about 10) in the items of 128 and of 256
+    queries: references move in most rows, and not in some."""
+    p = synth.make_block_weights(w)
+    for name in ("wq", "wk"):
+        p[name] = synth.storage_round(p[name] * np.float32(10.0 * np.sqrt(256 / w.D)), w.dtype)
+    _, x = synth.make_latents(w)
+    kv = OB.kv_projection(OB._f64(p), np.asarray(x, np.float64))
+    idx = np.arange(w.L)
+    rows = np.unique(np.r_[0, w.L - 1, np.arange(0, w.L, 29)])
+    q = OB.linear(kv[0][rows], OB._f64(p)["wq"], OB._f64(p)["bq"])
+    moves = _reference_moves(q, kv[1], w.H)
+    say(f"rescale {w.name}: rows whose reference moves {np.mean(moves > 0):.2f}, moves per row up to {moves.max()}")
+    assert np.mean(moves > 0) > 0.5 and np.mean(moves == 0) > 0.01
+    got = _block_gpu(w, p, x, idx, form=f"attn_fwd_bf16_q{128 if w is ITEMS[0] else 256}")[rows]
+    check_block(got, OB.block_partial(p, x, idx[rows], w.H, kv=kv), w.dtype, f"rescale {w.name}")
 
 
 def test_block_gates_one_informational():
@@ -665,7 +707,10 @@ def test_cached_step_end_to_end_full_size(w):
 def test_block_row_independence_full_size():
     """With the batch-invariant flag any selection gives exactly the rows of
     the all-token block (GPU vs GPU, bit-exact): holds at any size, checked at
-    32760 tokens."""
+    32760 tokens, whose products run 256 x 256 tiles, against selections of
+    13104 tokens (the same tiles), of 3276 and 1000 (128 x 128 for the Q and O
+    projections and FFN down, 256 x 256 for FFN up) and of 100 and 1 (64 x 64 for
+    all of them)."""
     w = synth.WAN14B_480P
     p = synth.make_block_weights(w)
     _, x = synth.make_latents(w)
@@ -683,6 +728,10 @@ def test_block_row_independence_full_size():
     a = down(ys_all)[sub]
     b = down(ys_sub)
     assert np.array_equal(a.view(np.uint32), b.view(np.uint32))
+    for n in (3276, 1000, 100, 1):
+        few = np.sort(rng.choice(w.L, n, replace=False)).astype(np.int32)
+        ys = api.block_partial(P, X, up(few), n, w.H, batch_invariant=True)
+        assert torch.equal(ys, ys_all[torch.from_numpy(few.astype(np.int64)).to(ys_all.device)]), n
     c = down(ys_def)
     err = np.abs(c.astype(np.float64) - b)
     assert err.max() <= TOL_BF16_ABS, float(err.max())
