@@ -37,8 +37,13 @@ def _lib_handle():
 # addresses as the ints that the declared argument types convert (a 13-weight
 # block call 13.0 -> 7.1 us of Python).
 
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)   # not a public name
+
+
 def _stream() -> int:
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def _ptr(t):

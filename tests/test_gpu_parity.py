@@ -30,6 +30,15 @@ def _bits(a):
     return a.view(np.uint32) if a.dtype == np.float32 else a
 
 
+def test_stream_handle_of_both_names(monkeypatch):
+    """The current stream's handle, also where torch lacks the private name it is read by."""
+    st = torch.cuda.Stream(device())
+    with torch.cuda.stream(st):
+        assert api._stream() == st.cuda_stream
+        monkeypatch.setattr(api, "_raw_stream", None)
+        assert api._stream() == st.cuda_stream
+
+
 # ------------------------------------------------------------------- energy
 
 @pytest.mark.parametrize("profile,n,T", [
