@@ -743,12 +743,19 @@ __global__ void __launch_bounds__(256) gemm_splitk_reduce(GemmBf16Args p, int nt
 }
 
 // ---- launcher.  One tile size for a product, the one with the least
-// estimated time: microseconds per k-step of 64 and the fixed times below are
-// measured on MI355X (256 CUs) over 36 products of 75 .. 32760 rows, 256 ..
-// 13824 columns and depths 256 .. 13824.  Over them the choice is the fastest
-// of the measured or within 8% of it.  (Whole rounds of large tiles with the
-// other rows in small ones, in two launches, were within 2% of the better of
-// the two: not built.)
+// estimated time.  The constants of the estimates are fitted to times measured
+// on MI355X (256 CUs) of 936 products of 50 .. 13104 rows, 256 .. 13824 columns
+// and depths 256 .. 13824 with each of the three epilogues, in every tile and
+// split: nine in ten estimates within -16 and +13% (large tile 11 and 13%).
+// Over these products the choice takes 1.4% more than the fastest of the
+// measured on average, 8% more or less in 95 of 100, 22% at most (few rows of
+// depth 4096 and 5120, where the 32 x 64 tiles are taken and 128 x 128 in four
+// k-ranges would be better), and at most 10% more than the large tile with its
+// k-split.  Constants from the bias epilogue alone, without the terms for the
+// epilogue and for the operands' loads, chose up to 47% more, and up to 34% more
+// than the large tile: 1000 x 5120 x 5120 with gate and residual 103 us, now 80.
+// (Whole rounds of large tiles with the other rows in small ones, in two
+// launches, were within 2% of the better of the two: not built.)
 constexpr int kBK = 64, kBigTile = 256;
 
 enum GemmTile { TILE_256, TILE_128, TILE_128_K2, TILE_64, TILE_32x64_K2 };
@@ -781,52 +788,70 @@ int big_tail_split(int tiles, int nk, int ncu, size_t part_bytes) {
   return nsplit;
 }
 
-// 256 x 256 tiles: 1.46 us per k-step of a round, 7 us to fill and drain it.
-float big_us(int tiles, int nk, int ncu, int nsplit) {
+// 256 x 256 tiles: 1.52 us per k-step of a round (1.02 while CUs are idle) and
+// the time to store it.
+float big_us(int tiles, int nk, int ncu, int nsplit, int epi) {
+  constexpr float kStore[] = {3.1f, 8.3f, 12.5f};  // bias, GELU, gate + residual
   const int full = tiles / ncu, pieces = (tiles % ncu) * nsplit;
-  float us = 3.0f + full * (1.46f * nk + 7.0f);
+  float us = 9.1f + full * (1.52f * nk + kStore[epi]);
   if (pieces > 0) {
+    const float load = full == 0 && pieces < ncu ? static_cast<float>(pieces) / ncu : 1.0f;
     // few pieces run beside the first whole tiles: about half of their time shows
-    const float r = nsplit > 1 && full > 0 && 4 * pieces < ncu ? 0.5f : 1.0f;
-    us += r * (1.46f * ((nk + nsplit - 1) / nsplit) + 7.0f);
-    if (nsplit > 1) us += 3.0f + 0.06f * pieces;  // 256 KB of partial sums per piece, written and reduced
+    const float r = nsplit > 1 && full > 0 && 4 * pieces < ncu ? 0.55f : 1.0f;
+    us += r * ((1.02f + 0.5f * load) * ((nk + nsplit - 1) / nsplit) + kStore[nsplit > 1 ? 0 : epi]);
+    if (nsplit > 1) us += 2.3f + 0.057f * pieces;  // 256 KB of partial sums per piece, written and reduced
   }
   return us;
 }
 
-// Smaller tiles: `pieces` workgroups, n on the busiest CU, two (128 x 128) or
-// three (the others) at a time.
 inline int tile_rows(GemmTile t) { return t == TILE_32x64_K2 ? 32 : t == TILE_64 ? 64 : 128; }
 inline int tile_cols(GemmTile t) { return t == TILE_64 || t == TILE_32x64_K2 ? 64 : 128; }
 inline int tile_count(GemmTile t, int M, int N) { return ((M + tile_rows(t) - 1) / tile_rows(t)) * (N / tile_cols(t)); }
-float small_us(GemmTile t, int pieces, int nk, int nsplit, int ncu) {
-  const int n = (pieces + ncu - 1) / ncu, steps = (nk + nsplit - 1) / nsplit;
-  float us;
-  if (t == TILE_128) {
-    // one workgroup alone 0.63 us per k-step, two together 1.02 (less while not every CU has two)
-    const float load = static_cast<float>(pieces) / ncu;
-    us = 3.0f + steps * (n == 2 ? 0.63f + 0.4f * (load - 1.0f) : 1.02f * (n / 2) + 0.63f * (n % 2));
-  } else if (t == TILE_128_K2) {
-    us = 1.0f + n * (0.5f * (steps + 1) + 3.0f);
-  } else if (t == TILE_64) {
-    us = 2.3f + steps * (0.56f * (n / 3) + (n % 3 == 2 ? 0.42f : n % 3 == 1 ? 0.27f : 0.0f));
-  } else {
-    us = 2.3f + 0.5f * (steps + 1) * (0.83f * (n / 3) + (n % 3 == 2 ? 0.45f : n % 3 == 1 ? 0.27f : 0.0f));
+
+// Smaller tiles: `pieces` workgroups, up to `resident` on a CU at a time.
+struct TileCost {
+  int resident;
+  float start;      // launch, fill
+  float step[3];    // a k-step with one, two, three workgroups on the busiest CU ...
+  float loads;      // ... and what it grows by with the operand rows that all workgroups load, per million
+  float store[3];   // a round's epilogue: bias, GELU, gate + residual
+  float min_store;  // at least this share of it
+};
+constexpr TileCost kTileCost[] = {
+    {},                                                                                            // TILE_256
+    {2, 5.95f, {0.528f, 0.469f}, 3.66f, {0.89f, 3.23f, 9.86f}, 0.38f},                             // TILE_128
+    {1, 5.56f, {0.846f}, 5.0f, {0.70f, 1.92f, 3.76f}, 0.56f},                                      // TILE_128_K2
+    {3, 4.97f, {0.386f, 0.439f, 0.380f}, 1.72f, {0.14f, 0.76f, 3.56f}, 0.32f},                     // TILE_64
+    {3, 5.13f, {0.416f, 0.546f, 0.553f}, 2.94f, {0.35f, 0.64f, 1.82f}, 0.0f},                      // TILE_32x64_K2
+};
+float small_us(GemmTile t, int pieces, int nk, int nsplit, int ncu, int epi) {
+  const TileCost& c = kTileCost[t];
+  float steps = static_cast<float>((nk + nsplit - 1) / nsplit);
+  if (t == TILE_128_K2 || t == TILE_32x64_K2) steps = 0.5f * (steps + 1.0f);  // two groups side by side
+  const int per_round = c.resident * ncu, full = pieces / per_round, rest = pieces % per_round;
+  float step = full * c.step[c.resident - 1];
+  if (rest > 0) {  // between the steps of i and of i + 1 workgroups per CU
+    const float load = static_cast<float>(rest) / ncu;
+    const int i = (rest - 1) / ncu;
+    step += i == 0 ? c.step[0] : c.step[i - 1] + (c.step[i] - c.step[i - 1]) * (load - i);
   }
+  const float rounds = static_cast<float>(pieces) / per_round;
+  float us = c.start + steps * (step + 1e-6f * c.loads * pieces * (tile_rows(t) + tile_cols(t))) +
+             c.store[nsplit > 1 ? 0 : epi] * (rounds > c.min_store ? rounds : c.min_store);
   // partial sums, reduce
-  if (nsplit > 1) us += 3.0f + 0.2e-6f * (static_cast<float>(pieces) * tile_rows(t) * tile_cols(t) * 4.0f);
+  if (nsplit > 1) us += 2.8f + 0.31e-6f * (static_cast<float>(pieces) * tile_rows(t) * tile_cols(t) * 4.0f);
   return us;
 }
 
 // part_bytes == 0 (no room for partial sums: every row must come out the same
 // for any M) leaves the plans that add the k-steps in order.
-GemmPlan gemm_plan(int M, int N, int K, int ncu, size_t part_bytes) {
+GemmPlan gemm_plan(int M, int N, int K, int epi, int ncu, size_t part_bytes) {
   const bool any_order = part_bytes > 0;
   const int nk = K / kBK, tiles = ((M + kBigTile - 1) / kBigTile) * (N / kBigTile);
   const int nsplit = any_order ? big_tail_split(tiles, nk, ncu, part_bytes) : 1;
-  GemmPlan best{TILE_256, nsplit, big_us(tiles, nk, ncu, nsplit)};
+  GemmPlan best{TILE_256, nsplit, big_us(tiles, nk, ncu, nsplit, epi)};
   auto consider = [&](GemmTile t, int sp) {
-    const float us = small_us(t, tile_count(t, M, N) * sp, nk, sp, ncu);
+    const float us = small_us(t, tile_count(t, M, N) * sp, nk, sp, ncu, epi);
     if (us < best.us) best = GemmPlan{t, sp, us};
   };
   consider(TILE_128, 1);
@@ -897,7 +922,7 @@ hipError_t launch_gemm_big(GemmBf16Args a, int nsplit, int ncu, hipStream_t stre
 template <int EPI>
 hipError_t launch_gemm_epi(const char* name, const GemmBf16Args& a, hipStream_t stream) {
   const int ncu = device_cu_count();
-  const GemmPlan plan = gemm_plan(a.M, a.N, a.K, ncu, a.part != nullptr ? a.part_bytes : 0);
+  const GemmPlan plan = gemm_plan(a.M, a.N, a.K, EPI, ncu, a.part != nullptr ? a.part_bytes : 0);
   ::echo::TimedLaunch scope(name, stream);
   switch (plan.tile) {
     case TILE_128: return launch_gemm_sm<128, 128, 1, EPI>(a, plan.nsplit, stream);
@@ -945,12 +970,12 @@ hipError_t launch_gemm_bf16_pair(const char* pair_name, const char* name_a, cons
   if (a.M > 0 && b.M > 0 && a.K == b.K && gemm_bf16_ok(a) && gemm_bf16_ok(b)) {
     const int ncu = device_cu_count(), nk = a.K / kBK;
     const bool any_order = a.part != nullptr;
-    const GemmPlan pa = gemm_plan(a.M, a.N, a.K, ncu, any_order ? a.part_bytes : 0);
-    const GemmPlan pb = gemm_plan(b.M, b.N, b.K, ncu, any_order ? b.part_bytes : 0);
+    const GemmPlan pa = gemm_plan(a.M, a.N, a.K, EPI_BIAS, ncu, any_order ? a.part_bytes : 0);
+    const GemmPlan pb = gemm_plan(b.M, b.N, b.K, EPI_BIAS, ncu, any_order ? b.part_bytes : 0);
     GemmPlan best{TILE_256, 1, pa.us + pb.us};  // TILE_256: separate launches
     const GemmTile tiles[] = {TILE_64, TILE_128, TILE_32x64_K2, TILE_128_K2};
     for (int i = 0; i < (any_order && nk % 2 == 0 ? 4 : 2); ++i) {
-      const float us = small_us(tiles[i], tile_count(tiles[i], a.M, a.N) + tile_count(tiles[i], b.M, b.N), nk, 1, ncu);
+      const float us = small_us(tiles[i], tile_count(tiles[i], a.M, a.N) + tile_count(tiles[i], b.M, b.N), nk, 1, ncu, EPI_BIAS);
       if (us < best.us) best = GemmPlan{tiles[i], 1, us};
     }
     if (best.tile != TILE_256) {
