@@ -744,16 +744,15 @@ __global__ void __launch_bounds__(256) gemm_splitk_reduce(GemmBf16Args p, int nt
 
 // ---- launcher.  One tile size for a product, the one with the least
 // estimated time.  The constants of the estimates are fitted to times measured
-// on MI355X (256 CUs) of 936 products of 50 .. 13104 rows, 256 .. 13824 columns
-// and depths 256 .. 13824 with each of the three epilogues, in every tile and
-// split: nine in ten estimates within -16 and +13% (large tile 11 and 13%).
-// Over these products the choice takes 1.4% more than the fastest of the
-// measured on average, 8% more or less in 95 of 100, 22% at most (few rows of
-// depth 4096 and 5120, where the 32 x 64 tiles are taken and 128 x 128 in four
-// k-ranges would be better), and at most 10% more than the large tile with its
-// k-split.  Constants from the bias epilogue alone, without the terms for the
-// epilogue and for the operands' loads, chose up to 47% more, and up to 34% more
-// than the large tile: 1000 x 5120 x 5120 with gate and residual 103 us, now 80.
+// on MI355X (256 CUs) of 3090 products of 30 .. 13104 rows, 256 .. 28928 columns
+// and depths 256 .. 28928 with each of the three epilogues, in every tile and
+// split.  Over these products the choice takes 0.6% more than the fastest of the
+// plans on average, 8% more or less in 98 of 100, 21% at most; against the large
+// tile with its k-split it is slower by 2% or more in 1 of 100.  Constants from
+// the bias epilogue of 36 products, without the terms for the epilogue and for
+// the operands' loads, chose 2.5% more on average and 57% at most, and were slower
+// than the large tile by 2% or more in 4 of 100, up to 34% (1000 x 5120 x 5120 with
+// gate and residual 103 us, now 80).
 // (Whole rounds of large tiles with the other rows in small ones, in two
 // launches, were within 2% of the better of the two: not built.)
 constexpr int kBK = 64, kBigTile = 256;
@@ -788,18 +787,26 @@ int big_tail_split(int tiles, int nk, int ncu, size_t part_bytes) {
   return nsplit;
 }
 
-// 256 x 256 tiles: 1.52 us per k-step of a round (1.02 while CUs are idle) and
-// the time to store it.
-float big_us(int tiles, int nk, int ncu, int nsplit, int epi) {
-  constexpr float kStore[] = {3.1f, 8.3f, 12.5f};  // bias, GELU, gate + residual
+// How far the weight is past the L2s (32 MB in all): 0 .. 1.  A k-step's loads
+// then come from beyond them, which shows where few workgroups hide it.
+inline float cold_share(int N, int K) {
+  const float share = static_cast<float>(N) * static_cast<float>(K) * 2.0f / (32 << 20);
+  return share < 1.0f ? share : 1.0f;
+}
+
+// 256 x 256 tiles: 1.4 us per k-step of a round (0.84 while CUs are idle, and
+// up to 0.09 more from beyond the L2s) and the time to store it.
+float big_us(int tiles, int nk, int ncu, int nsplit, int epi, float cold) {
+  constexpr float kStore[] = {3.47f, 13.7f, 12.5f};  // bias, GELU, gate + residual
   const int full = tiles / ncu, pieces = (tiles % ncu) * nsplit;
-  float us = 9.1f + full * (1.52f * nk + kStore[epi]);
+  float us = 8.0f + full * (1.4f * nk + kStore[epi]);
   if (pieces > 0) {
-    const float load = full == 0 && pieces < ncu ? static_cast<float>(pieces) / ncu : 1.0f;
-    // few pieces run beside the first whole tiles: about half of their time shows
-    const float r = nsplit > 1 && full > 0 && 4 * pieces < ncu ? 0.55f : 1.0f;
-    us += r * ((1.02f + 0.5f * load) * ((nk + nsplit - 1) / nsplit) + kStore[nsplit > 1 ? 0 : epi]);
-    if (nsplit > 1) us += 2.3f + 0.057f * pieces;  // 256 KB of partial sums per piece, written and reduced
+    const float idle = full == 0 && pieces < ncu ? 1.0f - static_cast<float>(pieces) / ncu : 0.0f;
+    const float step = 1.4f - 0.563f * idle + (full == 0 ? 0.087f * cold : 0.0f);
+    // few pieces run beside the first whole tiles: three quarters of their time shows
+    const float r = nsplit > 1 && full > 0 && 4 * pieces < ncu ? 0.75f : 1.0f;
+    us += r * (step * ((nk + nsplit - 1) / nsplit) + kStore[nsplit > 1 ? 0 : epi]);
+    if (nsplit > 1) us += 2.1f + 0.082f * pieces;  // 256 KB of partial sums per piece, written and reduced
   }
   return us;
 }
@@ -808,38 +815,38 @@ inline int tile_rows(GemmTile t) { return t == TILE_32x64_K2 ? 32 : t == TILE_64
 inline int tile_cols(GemmTile t) { return t == TILE_64 || t == TILE_32x64_K2 ? 64 : 128; }
 inline int tile_count(GemmTile t, int M, int N) { return ((M + tile_rows(t) - 1) / tile_rows(t)) * (N / tile_cols(t)); }
 
-// Smaller tiles: `pieces` workgroups, up to `resident` on a CU at a time.
+// Smaller tiles: `pieces` workgroups, up to `resident` on a CU at a time.  Times
+// in microseconds; a round is `resident` workgroups on every CU.
 struct TileCost {
   int resident;
-  float start;      // launch, fill
-  float step[3];    // a k-step with one, two, three workgroups on the busiest CU ...
-  float loads;      // ... and what it grows by with the operand rows that all workgroups load, per million
-  float store[3];   // a round's epilogue: bias, GELU, gate + residual
-  float min_store;  // at least this share of it
+  float start;                  // launch, fill
+  float first[3], more[3];      // a k-step of 1, 2, 3 workgroups on the busiest CU: in the first round, in later ones
+  float cold_first, cold_more;  // what it grows by with the weight beyond the L2s: in the first round, per later one
+  float loads;                  // and with the operand rows that all workgroups load, per million
+  float store[3], min_store;    // a round's epilogue: bias, GELU, gate + residual; at least this many rounds' worth
 };
 constexpr TileCost kTileCost[] = {
-    {},                                                                                            // TILE_256
-    {2, 5.95f, {0.528f, 0.469f}, 3.66f, {0.89f, 3.23f, 9.86f}, 0.38f},                             // TILE_128
-    {1, 5.56f, {0.846f}, 5.0f, {0.70f, 1.92f, 3.76f}, 0.56f},                                      // TILE_128_K2
-    {3, 4.97f, {0.386f, 0.439f, 0.380f}, 1.72f, {0.14f, 0.76f, 3.56f}, 0.32f},                     // TILE_64
-    {3, 5.13f, {0.416f, 0.546f, 0.553f}, 2.94f, {0.35f, 0.64f, 1.82f}, 0.0f},                      // TILE_32x64_K2
+    {},  // TILE_256
+    {2, 4.55f, {0.498f, 0.549f}, {0.594f, 0.609f}, 0.073f, 0.0f, 2.82f, {0.956f, 1.79f, 3.51f}, 1.78f},  // TILE_128
+    {1, 6.11f, {0.757f}, {1.11f}, 0.186f, 0.0f, 4.03f, {1.59f, 1.51f, 4.8f}, 0.747f},                    // TILE_128_K2
+    {3, 4.83f, {0.364f, 0.358f, 0.35f}, {0.0977f, 0.279f, 0.265f}, 0.0859f, 0.0581f, 1.7f,
+     {1.28f, 2.14f, 4.7f}, 0.344f},                                                                      // TILE_64
+    {3, 5.27f, {0.393f, 0.437f, 0.589f}, {0.285f, 0.391f, 0.534f}, 0.124f, 0.0826f, 1.38f,
+     {1.15f, 1.09f, 3.07f}, 0.0f},                                                                       // TILE_32x64_K2
 };
-float small_us(GemmTile t, int pieces, int nk, int nsplit, int ncu, int epi) {
+float small_us(GemmTile t, int pieces, int nk, int nsplit, int ncu, int epi, float cold) {
   const TileCost& c = kTileCost[t];
   float steps = static_cast<float>((nk + nsplit - 1) / nsplit);
   if (t == TILE_128_K2 || t == TILE_32x64_K2) steps = 0.5f * (steps + 1.0f);  // two groups side by side
-  const int per_round = c.resident * ncu, full = pieces / per_round, rest = pieces % per_round;
-  float step = full * c.step[c.resident - 1];
-  if (rest > 0) {  // between the steps of i and of i + 1 workgroups per CU
-    const float load = static_cast<float>(rest) / ncu;
-    const int i = (rest - 1) / ncu;
-    step += i == 0 ? c.step[0] : c.step[i - 1] + (c.step[i] - c.step[i - 1]) * (load - i);
-  }
-  const float rounds = static_cast<float>(pieces) / per_round;
-  float us = c.start + steps * (step + 1e-6f * c.loads * pieces * (tile_rows(t) + tile_cols(t))) +
-             c.store[nsplit > 1 ? 0 : epi] * (rounds > c.min_store ? rounds : c.min_store);
+  const int w = c.resident, n = (pieces + ncu - 1) / ncu, full = n / w, rest = n % w;
+  float step = c.first[full == 0 ? rest - 1 : w - 1];
+  if (full > 0) step += (full - 1) * c.more[w - 1] + (rest > 0 ? c.more[rest - 1] : 0.0f);
+  step += cold * (c.cold_first + c.cold_more * static_cast<float>(n - 1) / w);
+  step += 1e-6f * c.loads * static_cast<float>(pieces) * (tile_rows(t) + tile_cols(t));
+  const float rounds = static_cast<float>(pieces) / (w * ncu);
+  float us = c.start + steps * step + c.store[nsplit > 1 ? 0 : epi] * (rounds > c.min_store ? rounds : c.min_store);
   // partial sums, reduce
-  if (nsplit > 1) us += 2.8f + 0.31e-6f * (static_cast<float>(pieces) * tile_rows(t) * tile_cols(t) * 4.0f);
+  if (nsplit > 1) us += 2.7f + 0.317e-6f * (static_cast<float>(pieces) * tile_rows(t) * tile_cols(t) * 4.0f);
   return us;
 }
 
@@ -849,9 +856,10 @@ GemmPlan gemm_plan(int M, int N, int K, int epi, int ncu, size_t part_bytes) {
   const bool any_order = part_bytes > 0;
   const int nk = K / kBK, tiles = ((M + kBigTile - 1) / kBigTile) * (N / kBigTile);
   const int nsplit = any_order ? big_tail_split(tiles, nk, ncu, part_bytes) : 1;
-  GemmPlan best{TILE_256, nsplit, big_us(tiles, nk, ncu, nsplit, epi)};
+  const float cold = cold_share(N, K);
+  GemmPlan best{TILE_256, nsplit, big_us(tiles, nk, ncu, nsplit, epi, cold)};
   auto consider = [&](GemmTile t, int sp) {
-    const float us = small_us(t, tile_count(t, M, N) * sp, nk, sp, ncu, epi);
+    const float us = small_us(t, tile_count(t, M, N) * sp, nk, sp, ncu, epi, cold);
     if (us < best.us) best = GemmPlan{t, sp, us};
   };
   consider(TILE_128, 1);
@@ -862,8 +870,12 @@ GemmPlan gemm_plan(int M, int N, int K, int epi, int ncu, size_t part_bytes) {
     consider(TILE_32x64_K2, 1);
   }
   const size_t bytes = static_cast<size_t>((M + 127) / 128) * 128 * N * sizeof(float);
-  for (int sp = 2; sp <= 4; ++sp)  // at least 640 of depth per range, as above
-    if (nk / sp >= 10 && bytes * sp <= part_bytes) consider(TILE_128, sp);
+  // at least 640 of depth per range, as above, and no more than 64 MB of partial
+  // sums, whatever room the attention's list leaves (1809 x 4864 x 28928 in four
+  // ranges, 145 MB: estimated 2% faster than the large tile, measured 5% slower)
+  const size_t room = part_bytes < (size_t(64) << 20) ? part_bytes : size_t(64) << 20;
+  for (int sp = 2; sp <= 4; ++sp)
+    if (nk / sp >= 10 && bytes * sp <= room) consider(TILE_128, sp);
   return best;
 }
 
@@ -972,12 +984,17 @@ hipError_t launch_gemm_bf16_pair(const char* pair_name, const char* name_a, cons
     const bool any_order = a.part != nullptr;
     const GemmPlan pa = gemm_plan(a.M, a.N, a.K, EPI_BIAS, ncu, any_order ? a.part_bytes : 0);
     const GemmPlan pb = gemm_plan(b.M, b.N, b.K, EPI_BIAS, ncu, any_order ? b.part_bytes : 0);
-    GemmPlan best{TILE_256, 1, pa.us + pb.us};  // TILE_256: separate launches
-    const GemmTile tiles[] = {TILE_64, TILE_128, TILE_32x64_K2, TILE_128_K2};
+    const GemmTile tiles[] = {TILE_128, TILE_64, TILE_32x64_K2, TILE_128_K2};
+    GemmPlan best{TILE_256, 1, 3.0e38f};
     for (int i = 0; i < (any_order && nk % 2 == 0 ? 4 : 2); ++i) {
-      const float us = small_us(tiles[i], tile_count(tiles[i], a.M, a.N) + tile_count(tiles[i], b.M, b.N), nk, 1, ncu, EPI_BIAS);
+      const float us = small_us(tiles[i], tile_count(tiles[i], a.M, a.N) + tile_count(tiles[i], b.M, b.N), nk, 1, ncu,
+                                EPI_BIAS, cold_share(a.N + b.N, a.K));
       if (us < best.us) best = GemmPlan{tiles[i], 1, us};
     }
+    // the estimates of the smallest tiles have to be 6% better: over 748 pairs of 30 ..
+    // 11184 rows the choice is then 28% faster than two launches on average and 4%
+    // slower at most (11% without)
+    if (best.us >= (pa.us + pb.us) * (best.tile == TILE_128 ? 1.0f : 0.94f)) best.tile = TILE_256;  // two launches
     if (best.tile != TILE_256) {
       ::echo::TimedLaunch scope(pair_name, stream);
       switch (best.tile) {
