@@ -743,16 +743,19 @@ __global__ void __launch_bounds__(256) gemm_splitk_reduce(GemmBf16Args p, int nt
 }
 
 // ---- launcher.  One tile size for a product, the one with the least
-// estimated time.  The constants of the estimates are fitted to times measured
-// on MI355X (256 CUs) of 3090 products of 30 .. 13104 rows, 256 .. 28928 columns
-// and depths 256 .. 28928 with each of the three epilogues, in every tile and
-// split.  Over these products the choice takes 0.6% more than the fastest of the
-// plans on average, 8% more or less in 98 of 100, 21% at most; against the large
-// tile with its k-split it is slower by 2% or more in 1 of 100.  Constants from
-// the bias epilogue of 36 products, without the terms for the epilogue and for
-// the operands' loads, chose 2.5% more on average and 57% at most, and were slower
-// than the large tile by 2% or more in 4 of 100, up to 34% (1000 x 5120 x 5120 with
-// gate and residual 103 us, now 80).
+// estimated time.  The constants of the estimates are fitted to times on MI355X
+// (256 CUs) of products of 30 .. 13104 rows, 256 .. 28928 columns and depths 256 ..
+// 28928 in every tile and split, first timed alone (3090, with weights in the
+// caches and from HBM), then by what each plan changes in the time of a whole block
+// that runs again and again (5845 products of 1172 blocks of 200 .. 16000 tokens):
+// that is what counts, and events around a launch miss some of it, above all that a
+// split's reduce is a second launch that waits (3900 x 1536 x 8960: 129 us split
+// against 133 by events, 14 us more in its block).  Over these blocks a choice costs
+// 0.07% of the block against the fastest plan on average, 2% or less in 99 of 100, 12%
+// at most; against the large tile with its k-split it loses more than 1% in 4 of 1000.
+// Constants from the bias epilogue of 36 products, without the terms for the epilogue
+// and for the operands' loads, cost 0.37% on average, and chose tiles up to 34%
+// slower than the large one (1000 x 5120 x 5120 with gate and residual 103 us, now 80).
 // (Whole rounds of large tiles with the other rows in small ones, in two
 // launches, were within 2% of the better of the two: not built.)
 constexpr int kBK = 64, kBigTile = 256;
@@ -794,19 +797,20 @@ inline float cold_share(int N, int K) {
   return share < 1.0f ? share : 1.0f;
 }
 
-// 256 x 256 tiles: 1.4 us per k-step of a round (0.84 while CUs are idle, and
+// 256 x 256 tiles: 1.45 us per k-step of a round (0.96 while CUs are idle, and
 // up to 0.09 more from beyond the L2s) and the time to store it.
 float big_us(int tiles, int nk, int ncu, int nsplit, int epi, float cold) {
-  constexpr float kStore[] = {3.47f, 13.7f, 12.5f};  // bias, GELU, gate + residual
+  constexpr float kStore[] = {4.82f, 11.8f, 16.3f};  // bias, GELU, gate + residual
   const int full = tiles / ncu, pieces = (tiles % ncu) * nsplit;
-  float us = 8.0f + full * (1.4f * nk + kStore[epi]);
+  float us = 9.34f + full * (1.45f * nk + kStore[epi]);
   if (pieces > 0) {
     const float idle = full == 0 && pieces < ncu ? 1.0f - static_cast<float>(pieces) / ncu : 0.0f;
-    const float step = 1.4f - 0.563f * idle + (full == 0 ? 0.087f * cold : 0.0f);
-    // few pieces run beside the first whole tiles: three quarters of their time shows
-    const float r = nsplit > 1 && full > 0 && 4 * pieces < ncu ? 0.75f : 1.0f;
+    const float step = 1.45f - 0.494f * idle + (full == 0 ? 0.089f * cold : 0.0f);
+    // few pieces run beside the first whole tiles: little of their time shows
+    const float r = nsplit > 1 && full > 0 && 4 * pieces < ncu ? 0.075f : 1.0f;
     us += r * (step * ((nk + nsplit - 1) / nsplit) + kStore[nsplit > 1 ? 0 : epi]);
-    if (nsplit > 1) us += 2.1f + 0.082f * pieces;  // 256 KB of partial sums per piece, written and reduced
+    // the second launch; 256 KB of partial sums per piece, written and reduced
+    if (nsplit > 1) us += 15.9f + 0.078f * pieces;
   }
   return us;
 }
@@ -827,12 +831,12 @@ struct TileCost {
 };
 constexpr TileCost kTileCost[] = {
     {},  // TILE_256
-    {2, 4.55f, {0.498f, 0.549f}, {0.594f, 0.609f}, 0.073f, 0.0f, 2.82f, {0.956f, 1.79f, 3.51f}, 1.78f},  // TILE_128
-    {1, 6.11f, {0.757f}, {1.11f}, 0.186f, 0.0f, 4.03f, {1.59f, 1.51f, 4.8f}, 0.747f},                    // TILE_128_K2
-    {3, 4.83f, {0.364f, 0.358f, 0.35f}, {0.0977f, 0.279f, 0.265f}, 0.0859f, 0.0581f, 1.7f,
-     {1.28f, 2.14f, 4.7f}, 0.344f},                                                                      // TILE_64
-    {3, 5.27f, {0.393f, 0.437f, 0.589f}, {0.285f, 0.391f, 0.534f}, 0.124f, 0.0826f, 1.38f,
-     {1.15f, 1.09f, 3.07f}, 0.0f},                                                                       // TILE_32x64_K2
+    {2, 6.21f, {0.556f, 0.652f}, {0.684f, 0.776f}, 0.0722f, 0.0f, 1.78f, {1.94f, 4.3f, 9.81f}, 0.493f},  // TILE_128
+    {1, 5.74f, {0.961f}, {0.842f}, 0.152f, 0.0f, 3.87f, {1.1f, 1.88f, 4.31f}, 0.942f},                   // TILE_128_K2
+    {3, 4.84f, {0.435f, 0.488f, 0.505f}, {0.148f, 0.391f, 0.434f}, 0.0928f, 0.0291f, 1.06f,
+     {1.38f, 1.62f, 4.59f}, 0.32f},                                                                      // TILE_64
+    {3, 4.97f, {0.681f, 0.656f, 0.867f}, {0.383f, 0.438f, 0.569f}, 0.221f, 0.0784f, 1.03f,
+     {1.01f, 0.367f, 1.47f}, 0.122f},                                                                    // TILE_32x64_K2
 };
 float small_us(GemmTile t, int pieces, int nk, int nsplit, int ncu, int epi, float cold) {
   const TileCost& c = kTileCost[t];
@@ -845,8 +849,8 @@ float small_us(GemmTile t, int pieces, int nk, int nsplit, int ncu, int epi, flo
   step += 1e-6f * c.loads * static_cast<float>(pieces) * (tile_rows(t) + tile_cols(t));
   const float rounds = static_cast<float>(pieces) / (w * ncu);
   float us = c.start + steps * step + c.store[nsplit > 1 ? 0 : epi] * (rounds > c.min_store ? rounds : c.min_store);
-  // partial sums, reduce
-  if (nsplit > 1) us += 2.7f + 0.317e-6f * (static_cast<float>(pieces) * tile_rows(t) * tile_cols(t) * 4.0f);
+  // the second launch; partial sums, written and reduced
+  if (nsplit > 1) us += 9.9f + 0.285e-6f * (static_cast<float>(pieces) * tile_rows(t) * tile_cols(t) * 4.0f);
   return us;
 }
 
@@ -974,9 +978,11 @@ hipError_t launch_gemm_sm_pair(const GemmBf16Args& a, const GemmBf16Args& b, hip
 }
 
 // One launch where a tile of the smaller kind does both in less than their two
-// own plans take: always for a few hundred rows, where a launch costs as much
-// as its work (300 tokens of width 256, Q and K/V: 4.1 + 3.6 us -> 4.3),
-// and where one's last round leaves room for the other.
+// own plans are estimated to take: always for a few hundred rows, where a launch
+// costs as much as its work (300 tokens of width 256, Q and K/V: 4.1 + 3.6 us ->
+// 4.3), and where one's last round leaves room for the other.  Over 1172 blocks of
+// 200 .. 16000 tokens the choice takes 5% off the block against two launches on
+// average and costs 3% at most.
 hipError_t launch_gemm_bf16_pair(const char* pair_name, const char* name_a, const char* name_b,
                                  const GemmBf16Args& a, const GemmBf16Args& b, hipStream_t stream) {
   if (a.M > 0 && b.M > 0 && a.K == b.K && gemm_bf16_ok(a) && gemm_bf16_ok(b)) {
@@ -984,17 +990,13 @@ hipError_t launch_gemm_bf16_pair(const char* pair_name, const char* name_a, cons
     const bool any_order = a.part != nullptr;
     const GemmPlan pa = gemm_plan(a.M, a.N, a.K, EPI_BIAS, ncu, any_order ? a.part_bytes : 0);
     const GemmPlan pb = gemm_plan(b.M, b.N, b.K, EPI_BIAS, ncu, any_order ? b.part_bytes : 0);
+    GemmPlan best{TILE_256, 1, pa.us + pb.us};  // TILE_256: separate launches
     const GemmTile tiles[] = {TILE_128, TILE_64, TILE_32x64_K2, TILE_128_K2};
-    GemmPlan best{TILE_256, 1, 3.0e38f};
     for (int i = 0; i < (any_order && nk % 2 == 0 ? 4 : 2); ++i) {
       const float us = small_us(tiles[i], tile_count(tiles[i], a.M, a.N) + tile_count(tiles[i], b.M, b.N), nk, 1, ncu,
                                 EPI_BIAS, cold_share(a.N + b.N, a.K));
       if (us < best.us) best = GemmPlan{tiles[i], 1, us};
     }
-    // the estimates of the smallest tiles have to be 6% better: over 748 pairs of 30 ..
-    // 11184 rows the choice is then 28% faster than two launches on average and 4%
-    // slower at most (11% without)
-    if (best.us >= (pa.us + pb.us) * (best.tile == TILE_128 ? 1.0f : 0.94f)) best.tile = TILE_256;  // two launches
     if (best.tile != TILE_256) {
       ::echo::TimedLaunch scope(pair_name, stream);
       switch (best.tile) {
